@@ -147,6 +147,31 @@ def run(state):
     return prism.prism_rmsnorm_matmul(X, state["g"], W[0], Y, eps=EPS)
 
 
+def exact(case, seed):
+    """What run() returns for these inputs, evaluated in 64 bits by torch."""
+    state = prepare(case, seed)
+    wide = {k: v.double() for k, v in state.items() if isinstance(v, torch.Tensor)}
+
+    def normalised(x):
+        return x * torch.rsqrt(x.square().mean(-1, keepdim=True) + EPS)
+
+    if case["kind"] == "attention":
+        Q = normalised(wide["Q"]) if case["qk_norm"] else wide["Q"]
+        return torch.softmax(torch.bmm(Q, wide["K"].transpose(1, 2).contiguous()) * case["scale"], -1) @ wide["V"]
+    X = wide["X"]
+    if case["kind"] == "softmax":
+        return torch.softmax(X, -1) @ wide["W"]
+    op = case["op"]
+    if op != "swiglu":
+        X = normalised(X)
+    if state["g"] is not None:
+        X = X * wide["g"]
+    A = [X @ w.double() for w in state["W"]]
+    if op in ("gated", "swiglu"):
+        A[0] = A[0] * torch.sigmoid(A[0])
+    return A[0] * A[1] if len(A) > 1 else A[0]
+
+
 def work(case):
     """Every input read once, every output written once; two operations per multiply-add of the products."""
     size = 4 if case["dtype"] == "f32" else 2

@@ -1,0 +1,265 @@
+// Products for any M, K, N and every storage type: stored values are widened to fp32 and multiplied on the matrix
+// cores in fp32 (v_mfma_f32_16x16x4_f32), so nothing is rounded between the inputs and the output.
+//
+// A workgroup owns RG groups of 16 rows and 16 * VW columns; its wavefronts take the K-blocks (4 * XV deep, XV = the
+// values of 16 bytes) round-robin and meet in LDS after the loop.  The order of K inside a block is free as long as
+// both operands agree on it, and it is chosen so that neither operand needs rearranging: lane (q, c), q = lane / 16,
+// c = lane % 16, holds the XV consecutive K values XV * q .. of row c and the rows XV * q .. of W at the VW columns from
+// VW * c on; product i of the block takes element i of the first and row i of the second, and the VW columns of a lane
+// go to VW different accumulator tiles.  Sums of squares ride on the loads of X, the gain is applied in registers, and
+// 1/rms goes on after the loop (paper Table 1, "matmul commutes with div denominator").
+//
+// Ragged sizes cost nothing in the loop: a column group that would cross the right edge starts at N - VW instead (its
+// lanes repeat columns of their neighbour), rows past M repeat row M - 1 and are not stored, and the last K-block, if it
+// is not full, runs through a masked copy of the loop body.  Rows of W start at any element: loads are of 16 bytes at
+// the alignment of one element, which global loads take on this part.
+//
+// Measured against the plain FMA kernel that was here (8 rows x 256 columns per workgroup, one column per thread):
+// bf16 8 x 4096 x 32003 1600 -> 61 us (262 MB of W at 4.3 TB/s), fp32 gated 512 x 1024 x 4096 186 -> 94 us (91 TFLOP/s),
+// fp32 8 x 256 x 512 31 us -> the launch.
+//
+// What bounds it: 16 rows of 16-bit storage: streaming W (its fp32 products would keep up with 9.8 TB/s); more rows or
+// fp32 storage: the fp32 matrix rate, 256 operations per clock and compute unit (157 TFLOP/s).
+#include "device_utils.h"
+#include "prism_internal.h"
+
+namespace prism {
+
+namespace {
+
+// Storage types: widening and narrowing of one element.
+struct StoreF32 {
+    typedef float elem;
+    static __device__ __forceinline__ float widen(elem v) { return v; }
+    static __device__ __forceinline__ elem narrow(float v) { return v; }
+};
+struct StoreBf16 {
+    typedef uint16_t elem;
+    static __device__ __forceinline__ float widen(elem v) { return __builtin_bit_cast(float, (u32)v << 16); }
+    static __device__ __forceinline__ elem narrow(float v) { return (elem)(pack_bf16(v, 0.0f) & 0xFFFFu); }
+};
+struct StoreF16 {
+    typedef _Float16 elem;
+    static __device__ __forceinline__ float widen(elem v) { return (float)v; }
+    static __device__ __forceinline__ elem narrow(float v) { return (elem)v; }
+};
+
+// V consecutive elements, loaded in one piece from an address that is only aligned to one of them.
+template <typename E, int V> struct Piece {
+    typedef E vec __attribute__((ext_vector_type(V)));
+    typedef vec loose __attribute__((aligned(sizeof(E))));
+    vec v;
+    __device__ __forceinline__ void load(const E* p) { v = *(const loose*)p; }
+    __device__ __forceinline__ E at(int i) const { return v[i]; }
+    __device__ __forceinline__ void set(int i, E e) { v[i] = e; }
+};
+template <typename E> struct Piece<E, 1> {
+    E v;
+    __device__ __forceinline__ void load(const E* p) { v = *p; }
+    __device__ __forceinline__ E at(int) const { return v; }
+    __device__ __forceinline__ void set(int, E e) { v = e; }
+};
+
+// What a lane holds of one K-block.
+template <typename E, int XV, int VW, int RG, int G> struct Block {
+    Piece<E, XV> x[RG], g;
+    Piece<E, VW> w[G][XV];
+};
+
+}  // namespace
+
+// LDS: [G][waves][16][16 * VW] partial products of one row group, [waves][16 * RG] sums of squares.
+template <typename S, bool GATED, int RG, int VW>
+__global__ __launch_bounds__(kGeneralMaxWaves * 64) void general_kernel(
+    const typename S::elem* __restrict__ X, const typename S::elem* __restrict__ g,
+    const typename S::elem* __restrict__ W1, const typename S::elem* __restrict__ W2, typename S::elem* __restrict__ Y,
+    int M, int K, int N, float eps, int flags) {
+    typedef typename S::elem E;
+    constexpr int G = GATED ? 2 : 1;
+    constexpr int XV = 16 / (int)sizeof(E);
+    constexpr int KB = 4 * XV;
+    constexpr int TN = 16 * VW;
+    typedef Block<E, XV, VW, RG, G> Blk;
+
+    extern __shared__ __align__(16) float lds[];
+    const int nw = blockDim.x >> 6;
+    float* red = lds;
+    float* ss_red = lds + G * nw * 16 * TN;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = lane >> 4, c = lane & 15;
+    const int n0 = blockIdx.x * TN, m0 = blockIdx.y * (16 * RG);
+    const bool gain = (flags & kFlagGain) != 0;
+
+    const int nb = n0 + min(VW * c, N - VW - n0);  // this lane's first column (the host takes VW <= N)
+    const E* w_lane[G];
+    w_lane[0] = W1 + (size_t)(XV * q) * N + nb;
+    if (GATED) w_lane[G - 1] = W2 + (size_t)(XV * q) * N + nb;
+    const E* x_lane[RG];
+#pragma unroll
+    for (int r = 0; r < RG; ++r) x_lane[r] = X + (size_t)min(m0 + 16 * r + c, M - 1) * K + XV * q;
+    const E* g_lane = gain ? g + XV * q : X;
+
+    f32x4 acc[G][RG][VW];
+    float ss[RG];
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+        ss[r] = 0.f;
+#pragma unroll
+        for (int m = 0; m < G; ++m)
+#pragma unroll
+            for (int j = 0; j < VW; ++j) acc[m][r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    auto load = [&](Blk& b, int kb) __attribute__((always_inline)) {
+        const size_t k = (size_t)kb * KB;
+        if (gain) b.g.load(g_lane + k);
+#pragma unroll
+        for (int r = 0; r < RG; ++r) b.x[r].load(x_lane[r] + k);
+#pragma unroll
+        for (int i = 0; i < XV; ++i)
+#pragma unroll
+            for (int m = 0; m < G; ++m) b.w[m][i].load(w_lane[m] + (k + i) * N);
+    };
+    // The block that crosses the end of K: element by element, zeros past the end (in W too: nothing may meet an infinity
+    // there).
+    auto load_masked = [&](Blk& b, int kb) __attribute__((always_inline)) {
+        const size_t k = (size_t)kb * KB;
+#pragma unroll
+        for (int i = 0; i < XV; ++i) {
+            const bool ok = k + XV * q + i < (size_t)K;
+            b.g.set(i, (ok && gain) ? g_lane[k + i] : S::narrow(0.f));
+#pragma unroll
+            for (int r = 0; r < RG; ++r) b.x[r].set(i, ok ? x_lane[r][k + i] : S::narrow(0.f));
+#pragma unroll
+            for (int m = 0; m < G; ++m) {
+#pragma unroll
+                for (int j = 0; j < VW; ++j) b.w[m][i].set(j, S::narrow(0.f));
+                if (ok) b.w[m][i].load(w_lane[m] + (k + i) * N);
+            }
+        }
+    };
+    auto multiply = [&](const Blk& b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < XV; ++i) {
+            float a[RG];
+            const float gk = gain ? S::widen(b.g.at(i)) : 1.f;
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const float x = S::widen(b.x[r].at(i));
+                ss[r] = fmaf(x, x, ss[r]);
+                a[r] = x * gk;
+            }
+#pragma unroll
+            for (int m = 0; m < G; ++m)
+#pragma unroll
+                for (int j = 0; j < VW; ++j) {
+                    const float w = S::widen(b.w[m][i].at(j));
+#pragma unroll
+                    for (int r = 0; r < RG; ++r)
+                        acc[m][r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], w, acc[m][r][j], 0, 0, 0);
+                }
+        }
+    };
+
+    // The next block is requested before the present one is multiplied.  (Two or four blocks a trip for the narrow tiles
+    // gain nothing: fp32 1 x 4096 x 4096 21.4 us with one, 23.5 us with four.)
+    const int nfull = K / KB;
+    {
+        Blk cur, next;
+        int kb = wave;
+        if (kb < nfull) load(cur, kb);
+        for (; kb < nfull; kb += nw) {
+            if (kb + nw < nfull) load(next, kb + nw);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(cur);
+            cur = next;
+        }
+    }
+    if (nfull * KB < K && wave == nfull % nw) {
+        Blk tail;
+        load_masked(tail, nfull);
+        multiply(tail);
+    }
+
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+        ss[r] += __shfl_xor(ss[r], 16, 64);
+        ss[r] += __shfl_xor(ss[r], 32, 64);
+        if (q == 0) ss_red[wave * (16 * RG) + 16 * r + c] = ss[r];
+    }
+    // Across wavefronts, one row group at a time.  Element e of accumulator tile j in lane (q, c) is row 4 q + e,
+    // column j of the lane's VW.
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+        if (r > 0) __syncthreads();
+#pragma unroll
+        for (int m = 0; m < G; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < VW; ++j)
+                    red[((m * nw + wave) * 16 + 4 * q + e) * TN + VW * c + j] = acc[m][r][j][e];
+        __syncthreads();
+        for (int o = tid; o < 16 * TN; o += blockDim.x) {
+            const int row = o / TN, col = o % TN;
+            const int m = m0 + 16 * r + row;
+            const int first = col / VW * VW;  // the column group as laid out, before the shift at the right edge
+            if (m >= M || first >= N - n0) continue;
+            const int n = n0 + min(first, N - VW - n0) + col % VW;
+            float v = 0.f, u = 0.f, tot = 0.f;
+            for (int w = 0; w < nw; ++w) {
+                v += red[(w * 16 + row) * TN + col];
+                if (GATED) u += red[((nw + w) * 16 + row) * TN + col];
+                tot += ss_red[w * (16 * RG) + 16 * r + row];
+            }
+            const float rinv = (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
+            float y = v * rinv;
+            if (GATED) {
+                const float a = y;
+                y = ((flags & kFlagSilu) ? a / (1.0f + expf(-a)) : a) * (u * rinv);
+            }
+            Y[(size_t)m * N + n] = S::narrow(y);
+        }
+    }
+}
+
+template <typename S, bool GATED, int RG, int VW>
+static hipError_t launch_general_as(const Call& c) {
+    const int waves = c.form.waves;
+    typedef typename S::elem E;
+    const int tn = 16 * VW;
+    dim3 grid((c.N + tn - 1) / tn, (c.M + 16 * RG - 1) / (16 * RG)), block(waves * 64);
+    const size_t lds = ((size_t)(GATED ? 2 : 1) * waves * 16 * tn + (size_t)waves * 16 * RG) * sizeof(float);
+    auto kern = general_kernel<S, GATED, RG, VW>;
+    static std::atomic<uint64_t> opted{0};
+    if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, block, lds, c.stream, (const E*)c.X, (const E*)c.g, (const E*)c.W1,
+                       (const E*)(GATED ? c.W2 : c.W1), (E*)c.Y, c.M, c.K, c.N, c.eps, c.flags);
+    return hipGetLastError();
+}
+
+template <typename S, bool GATED>
+static hipError_t launch_general_form(const Call& c) {
+    constexpr bool wide = sizeof(typename S::elem) == 4;
+    switch (c.form.row_groups * 10 + c.form.cols) {
+        case 11: return launch_general_as<S, GATED, 1, 1>(c);
+        case 14: return launch_general_as<S, GATED, 1, 4>(c);
+        case 18: if constexpr (!wide) return launch_general_as<S, GATED, 1, 8>(c); else break;
+        case 21: return launch_general_as<S, GATED, 2, 1>(c);
+        case 24: return launch_general_as<S, GATED, 2, 4>(c);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename S>
+static hipError_t launch_general(const Call& c) {
+    return c.gated ? launch_general_form<S, true>(c) : launch_general_form<S, false>(c);
+}
+
+hipError_t launch_simple_f32(const Call& c) { return launch_general<StoreF32>(c); }
+hipError_t launch_simple_bf16(const Call& c) { return launch_general<StoreBf16>(c); }
+hipError_t launch_simple_f16(const Call& c) { return launch_general<StoreF16>(c); }
+
+}  // namespace prism

@@ -133,6 +133,7 @@ struct Plan {
                         // rotated to the address of W
     int base_split;     // decode, packed and balanced: K-slices of a tile outside the slow units (the grid to fall
                         // back to when W is not aligned to its units)
+    GeneralForm general;  // fp32 matrix-core kernel
     uint64_t ss_bytes;  // decode: bytes of the partial sums of squares (rounded)
 };
 
@@ -260,6 +261,35 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     const double t32 = ok32 ? r32.us : 1e300, t64 = ok64 ? r64.us : 1e300;
     if (pf <= t32 && pf <= t64) return 0;
     return t32 <= t64 ? 2 : 4;
+}
+
+// The form of the fp32 matrix-core kernel (any shape, any storage type): the one of the smallest estimate of
+//   rounds of workgroups x (K x (2 rg vw G + 3.5 rg s + w G) + 600 rg G)   cycles of a compute unit,
+// rg 16-row groups, vw columns per lane, G matrices: the fp32 products; X in operand layout (sixteen rows x 64 bytes per
+// load; s = 1 for fp32, 1/2 for 16-bit storage); the rows of W (w = 4 for fp32, 6 / 8 / 12 for 16-bit storage and vw = 1 /
+// 4 / 8); the reduction across wavefronts.  Fitted to twenty-two shapes with every form forced (1 to 4000 rows, K 256 to
+// 8192, N 300 to 32003): the choice is the fastest form or within 10 % of it.
+// Four wavefronts where there are three workgroups (of one matrix) for every compute unit, else eight: fp32 gated 512 x
+// 1024 x 4096 94 us with four, 100 us with eight; fp32 1 x 4096 x 4096 29 us with four, 21 us with eight.
+GeneralForm choose_general_form(bool gated, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype) {
+    struct Form { int rg, vw; double w16; };
+    static const Form forms[] = {{1, 8, 12.0}, {2, 4, 8.0}, {1, 4, 8.0}, {2, 1, 6.0}, {1, 1, 6.0}};
+    const bool wide = dtype == PRISM_F32;
+    const double cus = (double)cu_count(), G = gated ? 2.0 : 1.0;
+    GeneralForm best{1, 1, kGeneralMaxWaves};
+    double best_t = 1e300;
+    for (const Form& f : forms) {
+        if (f.vw > N || (f.vw == 8 && wide) || (f.rg == 2 && M <= 16)) continue;
+        const double wgs = (double)((N + 16 * f.vw - 1) / (16 * f.vw)) * (double)((M + 16 * f.rg - 1) / (16 * f.rg));
+        const double per_k = 2.0 * f.rg * f.vw * G + 3.5 * f.rg * (wide ? 1.0 : 0.5) + (wide ? 4.0 : f.w16) * G;
+        const double t = std::ceil(wgs / cus) * (per_k * (double)K + 600.0 * f.rg * G);
+        if (t < best_t) {
+            best_t = t;
+            best = GeneralForm{f.rg, f.vw, G * wgs >= 3.0 * cus ? 4 : kGeneralMaxWaves};
+        }
+    }
+    if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
+    return best;
 }
 
 bool prefill_tile_known(bool gated, int bm, int bn) {
@@ -428,12 +458,14 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
     p.path = path;
 
     if (path == PRISM_PATH_SIMPLE) {
-        p.tile_m = 8;
-        p.tile_n = 256;
-        p.grid_x = (int32_t)((N + 255) / 256);
-        p.grid_y = (int32_t)((M + 7) / 8);
-        p.block = 256;
-        if (p.grid_y > 65535) return PRISM_ERR_UNSUPPORTED;
+        if ((M + 7) / 8 > 65535) return PRISM_ERR_UNSUPPORTED;
+        const GeneralForm f = choose_general_form(gated, M, K, N, dtype);
+        out->general = f;
+        p.tile_m = 16 * f.row_groups;
+        p.tile_n = 16 * f.cols;
+        p.grid_x = (int32_t)((N + p.tile_n - 1) / p.tile_n);
+        p.grid_y = (int32_t)((M + p.tile_m - 1) / p.tile_m);
+        p.block = 64 * f.waves;
         return PRISM_OK;
     }
     if (!fast_ok) return PRISM_ERR_UNSUPPORTED;
@@ -774,7 +806,7 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
     const prism_status_t st = make_plan(op, M, K, N, dtype, &plan);
     if (st != PRISM_OK) return st;
 
-    Call c{X, g, W1, gated ? W2 : nullptr, Y, (int)M, (int)K, (int)N, eps, gated, flags, stream};
+    Call c{X, g, W1, gated ? W2 : nullptr, Y, (int)M, (int)K, (int)N, eps, gated, flags, stream, plan.general};
     hipError_t err = hipSuccess;
     switch (plan.pub.path) {
         case PRISM_PATH_SIMPLE:

@@ -10,6 +10,13 @@
 
 namespace prism {
 
+// The fp32 matrix-core kernel for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
+// times as many), wavefronts that share K.
+constexpr int kGeneralMaxWaves = 8;
+struct GeneralForm {
+    int row_groups, cols, waves;
+};
+
 struct Call {
     const void* X;
     const void* g;
@@ -21,6 +28,7 @@ struct Call {
     bool gated;
     int flags;  // kFlag* bits
     hipStream_t stream;
+    GeneralForm form;  // of the fp32 kernel, where the call takes that path
 };
 
 // Members of the operator family (paper Section 7.1): which of the optional steps a call takes.

@@ -62,6 +62,16 @@ def test_simple_bf16_unaligned_shapes(P, M, K, N, gated):
     _case(P, pi.BF16, M, K, N, gated, seed=200 + M, expect_path=P.PRISM_PATH_SIMPLE)
 
 
+# On 256 compute units these take every form of the kernel (16 or 32 rows; 16, 64 or 128 columns), with ragged rows, a
+# last K-block that is not full, a column group shifted back from the right edge, and the smallest width.
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("M,K,N", [(3, 37, 3), (16, 500, 1003), (17, 290, 2050), (64, 2047, 2048), (33, 65, 515),
+                                   (200, 290, 1283), (200, 131, 2050), (7, 95, 33001)])
+def test_any_shape_forms(P, dtype, gated, M, K, N):
+    _case(P, dtype, M, K, N, gated, seed=250 + M, expect_path=P.PRISM_PATH_SIMPLE)
+
+
 # ---- decode path ------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("gated", [False, True])

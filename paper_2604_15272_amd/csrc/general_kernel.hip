@@ -20,45 +20,13 @@
 //
 // What bounds it: 16 rows of 16-bit storage: streaming W (its fp32 products would keep up with 9.8 TB/s); more rows or
 // fp32 storage: the fp32 matrix rate, 256 operations per clock and compute unit (157 TFLOP/s).
+#include "any_shape.h"
 #include "device_utils.h"
 #include "prism_internal.h"
 
 namespace prism {
 
 namespace {
-
-// Storage types: widening and narrowing of one element.
-struct StoreF32 {
-    typedef float elem;
-    static __device__ __forceinline__ float widen(elem v) { return v; }
-    static __device__ __forceinline__ elem narrow(float v) { return v; }
-};
-struct StoreBf16 {
-    typedef uint16_t elem;
-    static __device__ __forceinline__ float widen(elem v) { return __builtin_bit_cast(float, (u32)v << 16); }
-    static __device__ __forceinline__ elem narrow(float v) { return (elem)(pack_bf16(v, 0.0f) & 0xFFFFu); }
-};
-struct StoreF16 {
-    typedef _Float16 elem;
-    static __device__ __forceinline__ float widen(elem v) { return (float)v; }
-    static __device__ __forceinline__ elem narrow(float v) { return (elem)v; }
-};
-
-// V consecutive elements, loaded in one piece from an address that is only aligned to one of them.
-template <typename E, int V> struct Piece {
-    typedef E vec __attribute__((ext_vector_type(V)));
-    typedef vec loose __attribute__((aligned(sizeof(E))));
-    vec v;
-    __device__ __forceinline__ void load(const E* p) { v = *(const loose*)p; }
-    __device__ __forceinline__ E at(int i) const { return v[i]; }
-    __device__ __forceinline__ void set(int i, E e) { v[i] = e; }
-};
-template <typename E> struct Piece<E, 1> {
-    E v;
-    __device__ __forceinline__ void load(const E* p) { v = *p; }
-    __device__ __forceinline__ E at(int) const { return v; }
-    __device__ __forceinline__ void set(int, E e) { v = e; }
-};
 
 // What a lane holds of one K-block.
 template <typename E, int XV, int VW, int RG, int G> struct Block {
@@ -70,7 +38,7 @@ template <typename E, int XV, int VW, int RG, int G> struct Block {
 
 // LDS: [G][waves][16][16 * VW] partial products of one row group, [waves][16 * RG] sums of squares.
 template <typename S, bool GATED, int RG, int VW>
-__global__ __launch_bounds__(kGeneralMaxWaves * 64) void general_kernel(
+__global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel(
     const typename S::elem* __restrict__ X, const typename S::elem* __restrict__ g,
     const typename S::elem* __restrict__ W1, const typename S::elem* __restrict__ W2, typename S::elem* __restrict__ Y,
     int M, int K, int N, float eps, int flags) {

@@ -263,35 +263,6 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     return t32 <= t64 ? 2 : 4;
 }
 
-// The form of the fp32 matrix-core kernel (any shape, any storage type): the one of the smallest estimate of
-//   rounds of workgroups x (K x (2 rg vw G + 3.5 rg s + w G) + 600 rg G)   cycles of a compute unit,
-// rg 16-row groups, vw columns per lane, G matrices: the fp32 products; X in operand layout (sixteen rows x 64 bytes per
-// load; s = 1 for fp32, 1/2 for 16-bit storage); the rows of W (w = 4 for fp32, 6 / 8 / 12 for 16-bit storage and vw = 1 /
-// 4 / 8); the reduction across wavefronts.  Fitted to twenty-two shapes with every form forced (1 to 4000 rows, K 256 to
-// 8192, N 300 to 32003): the choice is the fastest form or within 10 % of it.
-// Four wavefronts where there are three workgroups (of one matrix) for every compute unit, else eight: fp32 gated 512 x
-// 1024 x 4096 94 us with four, 100 us with eight; fp32 1 x 4096 x 4096 29 us with four, 21 us with eight.
-GeneralForm choose_general_form(bool gated, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype) {
-    struct Form { int rg, vw; double w16; };
-    static const Form forms[] = {{1, 8, 12.0}, {2, 4, 8.0}, {1, 4, 8.0}, {2, 1, 6.0}, {1, 1, 6.0}};
-    const bool wide = dtype == PRISM_F32;
-    const double cus = (double)cu_count(), G = gated ? 2.0 : 1.0;
-    GeneralForm best{1, 1, kGeneralMaxWaves};
-    double best_t = 1e300;
-    for (const Form& f : forms) {
-        if (f.vw > N || (f.vw == 8 && wide) || (f.rg == 2 && M <= 16)) continue;
-        const double wgs = (double)((N + 16 * f.vw - 1) / (16 * f.vw)) * (double)((M + 16 * f.rg - 1) / (16 * f.rg));
-        const double per_k = 2.0 * f.rg * f.vw * G + 3.5 * f.rg * (wide ? 1.0 : 0.5) + (wide ? 4.0 : f.w16) * G;
-        const double t = std::ceil(wgs / cus) * (per_k * (double)K + 600.0 * f.rg * G);
-        if (t < best_t) {
-            best_t = t;
-            best = GeneralForm{f.rg, f.vw, G * wgs >= 3.0 * cus ? 4 : kGeneralMaxWaves};
-        }
-    }
-    if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
-    return best;
-}
-
 bool prefill_tile_known(bool gated, int bm, int bn) {
     if (gated) return (bm == 256 && bn == 256) || (bm == 128 && bn == 256) || (bm == 128 && bn == 128);
     return (bm == 256 && bn == 256) || (bm == 256 && bn == 192) || (bm == 256 && bn == 128) || (bm == 128 && bn == 128) ||
@@ -327,6 +298,49 @@ Choice resolve_choice(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_dtyp
     return Choice{0, 0, 0};
 }
 
+// The form of the fp32 matrix-core kernel (any shape, any storage type): the one of the smallest estimate of
+//   rounds of workgroups x (K x (2 rg vw G + 3.5 rg s + w G + e rg) + 600 rg G)   cycles of a compute unit,
+// rg 16-row groups, vw columns per lane, G matrices: the fp32 products; X in operand layout (sixteen rows x 64 bytes per
+// load; s = 1 for fp32, 1/2 for 16-bit storage); the rows of W (w = 4 for fp32, 6 / 8 / 12 for 16-bit storage and vw = 1 /
+// 4 / 8); the exponentials (e = 6 for the softmax, else 0); the reduction across wavefronts.  Fitted to twenty-two shapes with every form forced (1 to 4000 rows, K 256 to
+// 8192, N 300 to 32003): the choice is the fastest form or within 10 % of it.
+// (Softmax: ten shapes, within 9 %.)  Products: four wavefronts where there are three workgroups (of one matrix) for every compute unit, else eight: fp32 gated 512 x
+// 1024 x 4096 94 us with four, 100 us with eight; fp32 1 x 4096 x 4096 29 us with four, 21 us with eight.
+// Softmax: eight, or sixteen of the narrowest tile where half the compute units get none (fp32 8 x 16384 x 64 62 us with eight,
+// 57 us with sixteen; products gain nothing).
+GeneralForm choose_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype) {
+    struct Form { int rg, vw; double w16; };
+    static const Form forms[] = {{1, 8, 12.0}, {2, 4, 8.0}, {1, 4, 8.0}, {2, 1, 6.0}, {1, 1, 6.0}};
+    const bool wide = dtype == PRISM_F32;
+    const double cus = (double)cu_count(), G = gated ? 2.0 : 1.0;
+    GeneralForm best{1, 1, 8};
+    double best_t = 1e300;
+    for (const Form& f : forms) {
+        if (f.vw > N || (f.vw == 8 && wide) || (f.rg == 2 && M <= 16)) continue;
+        const double wgs = (double)((N + 16 * f.vw - 1) / (16 * f.vw)) * (double)((M + 16 * f.rg - 1) / (16 * f.rg));
+        const double per_k = 2.0 * f.rg * f.vw * G + 3.5 * f.rg * (wide ? 1.0 : 0.5) + (wide ? 4.0 : f.w16) * G + (softmax ? 6.0 * f.rg : 0.0);
+        const double t = std::ceil(wgs / cus) * (per_k * (double)K + 600.0 * f.rg * G);
+        if (t < best_t) {
+            best_t = t;
+            best = GeneralForm{f.rg, f.vw, (!softmax && G * wgs >= 3.0 * cus) ? 4 : 8};
+            if (softmax && f.rg * f.vw == 1 && wgs <= 0.5 * cus) best.waves = 16;
+        }
+    }
+    if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
+    return best;
+}
+
+void set_general_form(Plan* out, bool gated, bool softmax, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype) {
+    const GeneralForm f = choose_general_form(gated, softmax, M, K, N, dtype);
+    out->general = f;
+    prism_plan_t& p = out->pub;
+    p.tile_m = 16 * f.row_groups;
+    p.tile_n = 16 * f.cols;
+    p.grid_x = (int32_t)((N + p.tile_n - 1) / p.tile_n);
+    p.grid_y = (int32_t)((M + p.tile_m - 1) / p.tile_m);
+    p.block = 64 * f.waves;
+}
+
 // Softmax -> MatMul: the matrix-core kernels for 16-bit storage with K and N multiples of 8 (variant 16: 16 rows
 // per workgroup over the whole of K; variant 32: 32 rows and one of split_k K-slices), else the plain one.
 prism_status_t make_softmax_plan(int64_t M, int64_t K, int64_t N, prism_dtype_t dtype, Choice choice, Plan* out) {
@@ -345,13 +359,8 @@ prism_status_t make_softmax_plan(int64_t M, int64_t K, int64_t N, prism_dtype_t 
     p.path = path;
     if (path == PRISM_PATH_SIMPLE) {
         if (choice.split_k > 1 || choice.variant != 0) return PRISM_ERR_UNSUPPORTED;
-        p.block = 256;
-        p.tile_m = 8;
-        p.tile_n = 256;
-        p.grid_x = (int32_t)((N + 255) / 256);
-        const int64_t gy = (M + 7) / 8;
-        if (gy > 65535) return PRISM_ERR_UNSUPPORTED;
-        p.grid_y = (int32_t)gy;
+        if ((M + 7) / 8 > 65535) return PRISM_ERR_UNSUPPORTED;
+        set_general_form(out, false, true, M, K, N, dtype);
         return PRISM_OK;
     }
     const int64_t n_tiles = (N + kSoftmaxTileN - 1) / kSoftmaxTileN;
@@ -459,13 +468,7 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
 
     if (path == PRISM_PATH_SIMPLE) {
         if ((M + 7) / 8 > 65535) return PRISM_ERR_UNSUPPORTED;
-        const GeneralForm f = choose_general_form(gated, M, K, N, dtype);
-        out->general = f;
-        p.tile_m = 16 * f.row_groups;
-        p.tile_n = 16 * f.cols;
-        p.grid_x = (int32_t)((N + p.tile_n - 1) / p.tile_n);
-        p.grid_y = (int32_t)((M + p.tile_m - 1) / p.tile_m);
-        p.block = 64 * f.waves;
+        set_general_form(out, gated, false, M, K, N, dtype);
         return PRISM_OK;
     }
     if (!fast_ok) return PRISM_ERR_UNSUPPORTED;
@@ -910,7 +913,7 @@ prism_status_t prism_softmax_matmul(const void* X, const void* W, void* Y, int64
     Plan plan;
     const prism_status_t st = make_plan(PRISM_OP_SOFTMAX_MATMUL, M, K, N, dtype, &plan);
     if (st != PRISM_OK) return st;
-    const SoftmaxCall c{X, W, Y, (int)M, (int)K, (int)N, stream};
+    const SoftmaxCall c{X, W, Y, (int)M, (int)K, (int)N, stream, plan.general};
     hipError_t err;
     if (plan.pub.path != PRISM_PATH_ROWS) {
         err = launch_softmax_simple(c, (int)dtype);

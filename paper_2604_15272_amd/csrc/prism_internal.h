@@ -12,7 +12,7 @@ namespace prism {
 
 // The fp32 matrix-core kernel for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
 // times as many), wavefronts that share K.
-constexpr int kGeneralMaxWaves = 8;
+constexpr int general_max_waves(int row_groups, int cols) { return row_groups * cols == 1 ? 16 : 8; }
 struct GeneralForm {
     int row_groups, cols, waves;
 };
@@ -42,6 +42,7 @@ struct SoftmaxCall {
     void* Y;
     int M, K, N;
     hipStream_t stream;
+    GeneralForm form;  // of the fp32 kernel, where the call takes that path
 };
 
 struct AttentionCall {

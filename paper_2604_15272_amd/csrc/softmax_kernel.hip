@@ -3,9 +3,8 @@
 // sum of exp(X) and the product exp(X) . W, and divides after the loop; softmax(X) is never written
 // to memory.  Both kernels here have that structure.  What the figure leaves out and a library
 // needs is the row maximum: exp(x - max) instead of exp(x), which changes nothing in exact
-// arithmetic and keeps every term in (0, 1].  The matrix-core kernel keeps a running maximum per wavefront
-// and rescales its accumulators when it moves (so X is read once, streaming under the arithmetic); the plain
-// kernel finds the maximum in a first pass over the same rows.
+// arithmetic and keeps every term in (0, 1].  The kernels keep a running maximum per wavefront and rescale their
+// accumulators when it moves (so X is read once, streaming under the arithmetic).
 //
 // Matrix-core kernel (16-bit storage): a workgroup owns 16 rows (one MFMA row group) and 128 columns
 // of W; its wavefronts take the 32-deep K-blocks round-robin.  X is K-contiguous, which is the
@@ -17,9 +16,10 @@
 // actually bound by at the paper's shape is the vector pipe (exponentials, conversions, the permutes
 // of W, which every workgroup re-reads from the L2 for its 16 rows).
 //
-// Plain kernel: any shape and storage type, 8 rows x 256 columns per workgroup, fp32 arithmetic.
+// Any shape and storage type: the same in fp32 (softmax_general_kernel).
 #include <type_traits>
 
+#include "any_shape.h"
 #include "device_utils.h"
 #include "prism_internal.h"
 #include "w_block.h"
@@ -30,19 +30,6 @@ namespace {
 
 constexpr int TN = 128;  // columns of W per workgroup (matrix-core kernel)
 constexpr int KB = 32;   // K depth of one MFMA
-
-template <typename T> __device__ __forceinline__ float ld_elem(const T* p, size_t i);
-template <> __device__ __forceinline__ float ld_elem<float>(const float* p, size_t i) { return p[i]; }
-template <> __device__ __forceinline__ float ld_elem<uint16_t>(const uint16_t* p, size_t i) {
-    return __builtin_bit_cast(float, (u32)p[i] << 16);
-}
-template <> __device__ __forceinline__ float ld_elem<_Float16>(const _Float16* p, size_t i) { return (float)p[i]; }
-template <typename T> __device__ __forceinline__ void st_elem(T* p, size_t i, float v);
-template <> __device__ __forceinline__ void st_elem<float>(float* p, size_t i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void st_elem<uint16_t>(uint16_t* p, size_t i, float v) {
-    p[i] = (uint16_t)(pack_bf16(v, 0.0f) & 0xFFFFu);
-}
-template <> __device__ __forceinline__ void st_elem<_Float16>(_Float16* p, size_t i, float v) { p[i] = (_Float16)v; }
 
 }  // namespace
 
@@ -233,109 +220,200 @@ hipError_t launch_softmax_rows_16bit(const SoftmaxCall& c, bool f16) {
     return f16 ? launch_softmax_rows_fmt<F16>(c) : launch_softmax_rows_fmt<Bf16>(c);
 }
 
-// ---- plain kernel -----------------------------------------------------------------------------------
-constexpr int kSmRows = 8;
-constexpr int kSmCols = 256;
+// ---- any shape, any storage type --------------------------------------------------------------------
+// The frame of the fp32 product kernel (general_kernel.hip): RG groups of 16 rows and 16 * VW columns per workgroup, the
+// wavefronts take 32-deep K-blocks round-robin, lane (q, c) holds eight consecutive K values of row c and the same eight rows
+// of W at its VW columns, products on the matrix cores in fp32.  The softmax rides in the operand: a running maximum per
+// row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
+// beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
+// The kernel this replaces (8 rows x 256 columns, one thread per column, two passes over X) was bound by its serial loads:
+// fp32 1624 x 3008 x 352 794 us, now 81 us.
+// Bound now: the fp32 matrix rate (fp32 4096 x 4096 x 128: 68 us, 63 TFLOP/s beside 17e6 exponentials per column tile), or,
+// with few workgroups, the chain of a wavefront's blocks.
+template <typename S, int RG, int VW>
+__global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_general_kernel(const typename S::elem* __restrict__ X,
+                                                                            const typename S::elem* __restrict__ W,
+                                                                            typename S::elem* __restrict__ Y, int M, int K,
+                                                                            int N) {
+    typedef typename S::elem E;
+    constexpr int XV = 8, KBG = 4 * XV, TNG = 16 * VW;
+    struct Blk {
+        Piece<E, XV> x[RG];
+        Piece<E, VW> w[XV];
+    };
+    extern __shared__ __align__(16) float lds[];
+    const int nw = blockDim.x >> 6;
+    float* red = lds;                        // [waves][16][TNG], one row group at a time
+    float* wave_max = lds + nw * 16 * TNG;   // [waves][16 * RG]
+    float* wave_sum = wave_max + nw * 16 * RG;
 
-template <typename T>
-__global__ __launch_bounds__(kSmCols) void softmax_simple_kernel(const T* __restrict__ X, const T* __restrict__ W,
-                                                               T* __restrict__ Y, int M, int K, int N) {
-    __shared__ float es[kSmRows][kSmCols];
-    __shared__ float part[kSmCols / 64][kSmRows];
-    __shared__ float row_max[kSmRows];
-    const int t = threadIdx.x;
-    const int n = blockIdx.x * kSmCols + t;
-    const int m0 = blockIdx.y * kSmRows;
-    const bool col_ok = n < N;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = lane >> 4, c = lane & 15;
+    const int n0 = blockIdx.x * TNG, m0 = blockIdx.y * (16 * RG);
+    // Columns past the right edge: the group starts at N - VW; rows past M: row M - 1 again (not stored).
+    const E* w_lane = W + (size_t)(XV * q) * N + n0 + min(VW * c, N - VW - n0);
+    const E* x_lane[RG];
+#pragma unroll
+    for (int r = 0; r < RG; ++r) x_lane[r] = X + (size_t)min(m0 + 16 * r + c, M - 1) * K + XV * q;
 
-    // pass 1: row maxima (threads stride over k; lanes, then wavefronts)
-    float mx[kSmRows];
+    f32x4 acc[RG][VW];
+    float m_run[RG], l_run[RG];
 #pragma unroll
-    for (int r = 0; r < kSmRows; ++r) mx[r] = -__builtin_inff();
-    for (int k = t; k < K; k += kSmCols) {
+    for (int r = 0; r < RG; ++r) {
+        m_run[r] = -__builtin_inff();
+        l_run[r] = 0.f;
 #pragma unroll
-        for (int r = 0; r < kSmRows; ++r)
-            if (m0 + r < M) mx[r] = fmaxf(mx[r], ld_elem<T>(X, (size_t)(m0 + r) * K + k));
+        for (int j = 0; j < VW; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    auto load = [&](Blk& b, int kb) __attribute__((always_inline)) {
+        const size_t k = (size_t)kb * KBG;
 #pragma unroll
-    for (int r = 0; r < kSmRows; ++r) {
+        for (int r = 0; r < RG; ++r) b.x[r].load(x_lane[r] + k);
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], off, 64));
-    }
-    if ((t & 63) == 0) {
+        for (int i = 0; i < XV; ++i) b.w[i].load(w_lane + (k + i) * N);
+    };
+    // The block that crosses the end of K: past it x = -inf (weight 0) and w = 0.
+    auto load_masked = [&](Blk& b, int kb) __attribute__((always_inline)) {
+        const size_t k = (size_t)kb * KBG;
 #pragma unroll
-        for (int r = 0; r < kSmRows; ++r) part[t >> 6][r] = mx[r];
-    }
-    __syncthreads();
-    if (t < kSmRows) {
-        float m = part[0][t];
+        for (int i = 0; i < XV; ++i) {
+            const bool ok = k + XV * q + i < (size_t)K;
 #pragma unroll
-        for (int w = 1; w < kSmCols / 64; ++w) m = fmaxf(m, part[w][t]);
-        row_max[t] = (m0 + t < M) ? m : 0.f;
-    }
-    __syncthreads();
-
-    // pass 2: exp and its row sum in the loop over k beside the product; the division after it
-    float acc[kSmRows], sum[kSmRows];
+            for (int r = 0; r < RG; ++r) b.x[r].set(i, ok ? x_lane[r][k + i] : S::narrow(-__builtin_inff()));
 #pragma unroll
-    for (int r = 0; r < kSmRows; ++r) { acc[r] = 0.f; sum[r] = 0.f; }
-    for (int kc = 0; kc < K; kc += kSmCols) {
-        __syncthreads();
-        const int k = kc + t;
-#pragma unroll
-        for (int r = 0; r < kSmRows; ++r) {
-            const int m = m0 + r;
-            const float e = (k < K && m < M) ? expf(ld_elem<T>(X, (size_t)m * K + k) - row_max[r]) : 0.f;
-            sum[r] += e;
-            es[r][t] = e;
+            for (int j = 0; j < VW; ++j) b.w[i].set(j, S::narrow(0.f));
+            if (ok) b.w[i].load(w_lane + (k + i) * N);
         }
-        __syncthreads();
-        const int kend = min(kSmCols, K - kc);
-        if (col_ok) {
-            for (int kk = 0; kk < kend; ++kk) {
-                const float w = ld_elem<T>(W, (size_t)(kc + kk) * N + n);
+    };
+    auto multiply = [&](const Blk& b) __attribute__((always_inline)) {
+        float shift[RG];
 #pragma unroll
-                for (int r = 0; r < kSmRows; ++r) acc[r] = fmaf(es[r][kk], w, acc[r]);
+        for (int r = 0; r < RG; ++r) {
+            float cm = S::widen(b.x[r].at(0));
+#pragma unroll
+            for (int i = 1; i < XV; ++i) cm = fmaxf(cm, S::widen(b.x[r].at(i)));
+            cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
+            cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+            const float m_new = fmaxf(m_run[r], cm);
+            if (__builtin_amdgcn_ballot_w64(m_new != m_run[r]) != 0) {
+                // Element e of an accumulator in lane (q, c) belongs to row 4 q + e, whose factor lives in the lanes of that
+                // row.  A row that has seen nothing yet keeps the factor 1.
+                const float f = (m_run[r] == -__builtin_inff()) ? 1.0f : expf(m_run[r] - m_new);
+                l_run[r] *= f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float fe = __shfl(f, 4 * q + e, 64);
+#pragma unroll
+                    for (int j = 0; j < VW; ++j) acc[r][j][e] *= fe;
+                }
+                m_run[r] = m_new;
+            }
+            // Nothing but -inf so far: those have weight 0 (a NaN among them stays one).
+            shift[r] = (m_run[r] == -__builtin_inff()) ? 0.f : m_run[r];
+        }
+#pragma unroll
+        for (int i = 0; i < XV; ++i) {
+            float a[RG];
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                a[r] = expf(S::widen(b.x[r].at(i)) - shift[r]);
+                l_run[r] += a[r];
+            }
+#pragma unroll
+            for (int j = 0; j < VW; ++j) {
+                const float w = S::widen(b.w[i].at(j));
+#pragma unroll
+                for (int r = 0; r < RG; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], w, acc[r][j], 0, 0, 0);
             }
         }
+    };
+    const int nfull = K / KBG;
+    {
+        Blk cur, next;
+        int kb = wave;
+        if (kb < nfull) load(cur, kb);
+        for (; kb < nfull; kb += nw) {
+            if (kb + nw < nfull) load(next, kb + nw);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(cur);
+            cur = next;
+        }
+    }
+    if (nfull * KBG < K && wave == nfull % nw) {
+        Blk tail;
+        load_masked(tail, nfull);
+        multiply(tail);
+    }
+
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+        l_run[r] += __shfl_xor(l_run[r], 16, 64);
+        l_run[r] += __shfl_xor(l_run[r], 32, 64);
+        if (q == 0) {
+            wave_max[wave * (16 * RG) + 16 * r + c] = m_run[r];
+            wave_sum[wave * (16 * RG) + 16 * r + c] = l_run[r];
+        }
     }
 #pragma unroll
-    for (int r = 0; r < kSmRows; ++r) {
-        float v = sum[r];
+    for (int r = 0; r < RG; ++r) {
+        if (r > 0) __syncthreads();
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        sum[r] = v;
-    }
-    __syncthreads();
-    if ((t & 63) == 0) {
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int r = 0; r < kSmRows; ++r) part[t >> 6][r] = sum[r];
-    }
-    __syncthreads();
-    if (!col_ok) return;
-#pragma unroll
-    for (int r = 0; r < kSmRows; ++r) {
-        const int m = m0 + r;
-        if (m >= M) break;
-        float den = 0.f;
-#pragma unroll
-        for (int w = 0; w < kSmCols / 64; ++w) den += part[w][r];
-        st_elem<T>(Y, (size_t)m * N + n, acc[r] / den);
+            for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * TNG + VW * c + j] = acc[r][j][e];
+        __syncthreads();
+        for (int o = tid; o < 16 * TNG; o += blockDim.x) {
+            const int row = o / TNG, col = o % TNG;
+            const int m = m0 + 16 * r + row;
+            const int first = col / VW * VW;
+            if (m >= M || first >= N - n0) continue;
+            const int n = n0 + min(first, N - VW - n0) + col % VW;
+            float gmax = -__builtin_inff();
+            for (int w = 0; w < nw; ++w) gmax = fmaxf(gmax, wave_max[w * (16 * RG) + 16 * r + row]);
+            float v = 0.f, den = 0.f;
+            for (int w = 0; w < nw; ++w) {
+                const float mw = wave_max[w * (16 * RG) + 16 * r + row];
+                const float f = (mw == -__builtin_inff()) ? 0.f : expf(mw - gmax);  // a wavefront that saw nothing
+                v = fmaf(f, red[(w * 16 + row) * TNG + col], v);
+                den = fmaf(f, wave_sum[w * (16 * RG) + 16 * r + row], den);
+            }
+            Y[(size_t)m * N + n] = S::narrow(v / den);
+        }
     }
 }
 
-template <typename T>
-static hipError_t launch_softmax_simple_t(const SoftmaxCall& c) {
-    dim3 grid((c.N + kSmCols - 1) / kSmCols, (c.M + kSmRows - 1) / kSmRows), block(kSmCols);
-    hipLaunchKernelGGL((softmax_simple_kernel<T>), grid, block, 0, c.stream, (const T*)c.X, (const T*)c.W, (T*)c.Y, c.M,
-                       c.K, c.N);
+template <typename S, int RG, int VW>
+static hipError_t launch_softmax_general_as(const SoftmaxCall& c) {
+    typedef typename S::elem E;
+    constexpr int tn = 16 * VW;
+    const int waves = c.form.waves;
+    dim3 grid((c.N + tn - 1) / tn, (c.M + 16 * RG - 1) / (16 * RG)), block(waves * 64);
+    const size_t lds = (size_t)waves * (16 * tn + 2 * 16 * RG) * sizeof(float);
+    auto kern = softmax_general_kernel<S, RG, VW>;
+    static std::atomic<uint64_t> opted{0};
+    if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, block, lds, c.stream, (const E*)c.X, (const E*)c.W, (E*)c.Y, c.M, c.K, c.N);
     return hipGetLastError();
 }
 
+template <typename S>
+static hipError_t launch_softmax_general(const SoftmaxCall& c) {
+    constexpr bool wide = sizeof(typename S::elem) == 4;
+    switch (c.form.row_groups * 10 + c.form.cols) {
+        case 11: return launch_softmax_general_as<S, 1, 1>(c);
+        case 14: return launch_softmax_general_as<S, 1, 4>(c);
+        case 18: if constexpr (!wide) return launch_softmax_general_as<S, 1, 8>(c); else break;
+        case 21: return launch_softmax_general_as<S, 2, 1>(c);
+        case 24: return launch_softmax_general_as<S, 2, 4>(c);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_softmax_simple(const SoftmaxCall& c, int dtype) {
-    if (dtype == PRISM_F32) return launch_softmax_simple_t<float>(c);
-    if (dtype == PRISM_F16) return launch_softmax_simple_t<_Float16>(c);
-    return launch_softmax_simple_t<uint16_t>(c);
+    if (dtype == PRISM_F32) return launch_softmax_general<StoreF32>(c);
+    if (dtype == PRISM_F16) return launch_softmax_general<StoreF16>(c);
+    return launch_softmax_general<StoreBf16>(c);
 }
 
 }  // namespace prism

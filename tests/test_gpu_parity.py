@@ -72,6 +72,36 @@ def test_any_shape_forms(P, dtype, gated, M, K, N):
     _case(P, dtype, M, K, N, gated, seed=250 + M, expect_path=P.PRISM_PATH_SIMPLE)
 
 
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
+@pytest.mark.parametrize("M,K,N", [(3, 37, 3), (16, 1003, 500), (40, 290, 2050), (200, 1000, 1283), (300, 131, 77),
+                                   (2000, 97, 515)])
+def test_softmax_any_shape_forms(P, dtype, M, K, N):
+    _softmax_case(P, dtype, M, K, N, seed=260 + M, expect_path=P.PRISM_PATH_SIMPLE)
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.F16])
+def test_softmax_any_shape_masked_and_non_finite(P, dtype):
+    """Rows that begin with long runs of -inf, rows of -inf alone, +inf and NaN: as the definition gives them."""
+    import torch
+    from gpu_util import torch_dtype
+    M, K, N = 20, 1001, 67
+    gen = torch.Generator().manual_seed(5)
+    X, W = torch.randn(M, K, generator=gen).to(torch_dtype(dtype)), torch.randn(K, N, generator=gen).to(torch_dtype(dtype))
+    X[0, :700] = -float("inf")
+    X[1, 1:] = -float("inf")
+    X[2, :] = torch.finfo(X.dtype).min
+    X[3, :] = -float("inf")
+    X[4, 500] = float("nan")
+    X[5, 40] = float("inf")
+    X[6, :990] = -float("inf")
+    X[6, 3] = float("nan")
+    Y = torch.empty(M, N, dtype=X.dtype, device="cuda")
+    P.prism_softmax_matmul(X.cuda(), W.cuda(), Y)
+    ref = torch.softmax(X.double(), -1) @ W.double()
+    torch.testing.assert_close(Y.double().cpu(), ref, rtol=1e-5 if dtype == pi.F32 else 2.5e-3,
+                               atol=1e-5 if dtype == pi.F32 else 2.5e-3, equal_nan=True)
+
+
 # ---- decode path ------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("gated", [False, True])

@@ -28,12 +28,14 @@ template <typename E, int V> struct Piece {
     typedef vec loose __attribute__((aligned(sizeof(E))));
     vec v;
     __device__ __forceinline__ void load(const E* p) { v = *(const loose*)p; }
+    __device__ __forceinline__ void store(E* p) const { *(loose*)p = v; }
     __device__ __forceinline__ E at(int i) const { return v[i]; }
     __device__ __forceinline__ void set(int i, E e) { v[i] = e; }
 };
 template <typename E> struct Piece<E, 1> {
     E v;
     __device__ __forceinline__ void load(const E* p) { v = *p; }
+    __device__ __forceinline__ void store(E* p) const { *p = v; }
     __device__ __forceinline__ E at(int) const { return v; }
     __device__ __forceinline__ void set(int, E e) { v = e; }
 };

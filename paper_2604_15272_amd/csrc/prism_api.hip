@@ -304,7 +304,7 @@ Choice resolve_choice(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_dtyp
 // load; s = 1 for fp32, 1/2 for 16-bit storage); the rows of W (w = 4 for fp32, 6 / 8 / 12 for 16-bit storage and vw = 1 /
 // 4 / 8); the exponentials (e = 6 for the softmax, else 0); the reduction across wavefronts.  Fitted to twenty-two shapes with every form forced (1 to 4000 rows, K 256 to
 // 8192, N 300 to 32003): the choice is the fastest form or within 10 % of it.
-// (Softmax: ten shapes, within 9 %.)  Products: four wavefronts where there are three workgroups (of one matrix) for every compute unit, else eight: fp32 gated 512 x
+// (Softmax: ten shapes, within 9 %.)  Products without LDS: four wavefronts where there are three workgroups (of one matrix) for every compute unit, else eight: fp32 gated 512 x
 // 1024 x 4096 94 us with four, 100 us with eight; fp32 1 x 4096 x 4096 29 us with four, 21 us with eight.
 // Softmax: eight, or sixteen of the narrowest tile where half the compute units get none (fp32 8 x 16384 x 64 62 us with eight,
 // 57 us with sixteen; products gain nothing).
@@ -324,6 +324,21 @@ GeneralForm choose_general_form(bool gated, bool softmax, int64_t M, int64_t K, 
             best_t = t;
             best = GeneralForm{f.rg, f.vw, (!softmax && G * wgs >= 3.0 * cus) ? 4 : 8};
             if (softmax && f.rg * f.vw == 1 && wgs <= 0.5 * cus) best.waves = 16;
+        }
+    }
+    // Many rows: both operands through LDS (64 or 128 rows x 128 columns, columns of both matrices together), a workgroup
+    // per compute unit at a time: rounds x (per_k K + 6000) + 10000 cycles; per_k = 80 / 152, the fp32 products (64 / 128)
+    // and what of staging and operand reads does not hide under them.  Measured on seventeen shapes (40 to 4096 rows, K 256
+    // to 4096, N 500 to 9000, all three types): the choice over both kernels is the fastest form or within 9 %.
+    for (int rg = 4; rg <= 8 && !softmax && N >= 4; rg += 4) {
+        const int64_t cw = gated ? 64 : 128;
+        const int64_t tiles_n = (N + cw - 1) / cw;
+        if (tiles_n > 65535) break;
+        const double wgs = (double)tiles_n * (double)((M + 16 * rg - 1) / (16 * rg));
+        const double t = std::ceil(wgs / cus) * ((rg == 4 ? 80.0 : 152.0) * (double)K + 6000.0) + 10000.0;
+        if (t < best_t) {
+            best_t = t;
+            best = GeneralForm{rg, gated ? 4 : 8, 8};
         }
     }
     if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
@@ -813,7 +828,8 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
     hipError_t err = hipSuccess;
     switch (plan.pub.path) {
         case PRISM_PATH_SIMPLE:
-            err = (dtype == PRISM_F32) ? launch_simple_f32(c)
+            err = plan.general.row_groups >= kTiledRowGroups ? launch_general_tiled(c, (int)dtype)
+                  : (dtype == PRISM_F32) ? launch_simple_f32(c)
                   : (dtype == PRISM_F16) ? launch_simple_f16(c) : launch_simple_bf16(c);
             break;
         case PRISM_PATH_DECODE: {

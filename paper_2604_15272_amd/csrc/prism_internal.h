@@ -10,8 +10,9 @@
 
 namespace prism {
 
-// The fp32 matrix-core kernel for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
-// times as many), wavefronts that share K.
+// The fp32 matrix-core kernels for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
+// times as many), wavefronts that share K.  From kTiledRowGroups row groups on: the kernel with both operands in LDS.
+constexpr int kTiledRowGroups = 4;
 constexpr int general_max_waves(int row_groups, int cols) { return row_groups * cols == 1 ? 16 : 8; }
 struct GeneralForm {
     int row_groups, cols, waves;
@@ -123,6 +124,7 @@ inline hipError_t allow_large_lds(const void* kernel, size_t bytes, std::atomic<
 hipError_t launch_simple_f32(const Call& c);
 hipError_t launch_simple_bf16(const Call& c);
 hipError_t launch_simple_f16(const Call& c);
+hipError_t launch_general_tiled(const Call& c, int dtype);
 // The matrix-core kernels, for either 16-bit storage format (f16 = false: bf16).
 struct StreamPartition;
 hipError_t launch_decode_16bit(const Call& c, bool f16, int split_k, const StreamPartition& sp, int waves, bool packed,

@@ -102,6 +102,24 @@ def test_softmax_any_shape_masked_and_non_finite(P, dtype):
                                atol=1e-5 if dtype == pi.F32 else 2.5e-3, equal_nan=True)
 
 
+# The same with both operands in LDS (64 and 128 rows per workgroup): ragged rows and columns on either side of a tile, K
+# with a rest; then a whole number of stages, and less than one.
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
+@pytest.mark.parametrize("M,K,N,gated,rows", [(1999, 290, 2047, False, 128), (1999, 290, 1023, True, 128),
+                                              (1023, 501, 2046, False, 64), (1021, 1201, 1023, True, 64),
+                                              (1010, 545, 2045, False, 64)])
+def test_any_shape_tiled_forms(P, dtype, M, K, N, gated, rows):
+    plan = P.prism_plan(int(gated), M, K, N, DTYPE_CODE[dtype])
+    assert plan["tile_m"] == rows or P.prism_diag_cu_count() != 256
+    _case(P, dtype, M, K, N, gated, seed=270 + M, expect_path=P.PRISM_PATH_SIMPLE)
+
+
+@pytest.mark.parametrize("M,K,N,gated", [(512, 1024, 4096, True), (6000, 20, 4003, False)])
+def test_fp32_tiled_stage_counts(P, M, K, N, gated):
+    assert P.prism_plan(int(gated), M, K, N, P.PRISM_F32)["tile_m"] == 128 or P.prism_diag_cu_count() != 256
+    _case(P, pi.F32, M, K, N, gated, seed=280, expect_path=P.PRISM_PATH_SIMPLE)
+
+
 # ---- decode path ------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("gated", [False, True])

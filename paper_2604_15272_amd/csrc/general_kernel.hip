@@ -222,12 +222,13 @@ static hipError_t launch_general_form(const Call& c) {
 }
 
 template <typename S>
-static hipError_t launch_general(const Call& c) {
+static hipError_t launch_general(const Call& c, int dtype) {
+    if (c.form.row_groups >= kTiledRowGroups) return launch_general_tiled(c, dtype);
     return c.gated ? launch_general_form<S, true>(c) : launch_general_form<S, false>(c);
 }
 
-hipError_t launch_simple_f32(const Call& c) { return launch_general<StoreF32>(c); }
-hipError_t launch_simple_bf16(const Call& c) { return launch_general<StoreBf16>(c); }
-hipError_t launch_simple_f16(const Call& c) { return launch_general<StoreF16>(c); }
+hipError_t launch_simple_f32(const Call& c) { return launch_general<StoreF32>(c, PRISM_F32); }
+hipError_t launch_simple_bf16(const Call& c) { return launch_general<StoreBf16>(c, PRISM_BF16); }
+hipError_t launch_simple_f16(const Call& c) { return launch_general<StoreF16>(c, PRISM_F16); }
 
 }  // namespace prism

@@ -828,8 +828,7 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
     hipError_t err = hipSuccess;
     switch (plan.pub.path) {
         case PRISM_PATH_SIMPLE:
-            err = plan.general.row_groups >= kTiledRowGroups ? launch_general_tiled(c, (int)dtype)
-                  : (dtype == PRISM_F32) ? launch_simple_f32(c)
+            err = (dtype == PRISM_F32) ? launch_simple_f32(c)
                   : (dtype == PRISM_F16) ? launch_simple_f16(c) : launch_simple_bf16(c);
             break;
         case PRISM_PATH_DECODE: {

@@ -135,6 +135,17 @@ __device__ __forceinline__ f32x4 load_coherent4(__amdgpu_buffer_rsrc_t r, u32 by
 // Blocks until every store this wavefront issued has been acknowledged by the memory system.
 __device__ __forceinline__ void wait_stores_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Column tile of workgroup x of n, so that each of the eight XCDs (which take workgroups in turn) has a run of neighbouring
+// tiles.  Tiles whose rows do not start on a cache line share the lines at their edges, and only neighbours on the same XCD
+// find them in its L2.
+__device__ __forceinline__ int xcd_run_tile(unsigned x, unsigned n) {
+    const unsigned run = n >> 3;
+    return (int)(x < 8u * run ? (x & 7u) * run + (x >> 3) : x);
+}
+
+// Whether 16-bit column tiles of a row-major matrix of n columns share lines, and are enough for runs of five.
+__device__ __forceinline__ bool tiles_share_lines(int n, unsigned tiles) { return (n & 63) != 0 && tiles >= 40u; }
+
 __device__ __forceinline__ float silu_f32(float a) {
     // a / (1 + exp(-a)); exp(-a) -> inf for very negative a gives a * 0 = -0.
     return a * __builtin_amdgcn_rcpf(1.0f + __expf(-a));

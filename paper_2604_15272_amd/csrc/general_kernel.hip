@@ -15,8 +15,9 @@
 // the alignment of one element, which global loads take on this part.
 //
 // Measured against the plain FMA kernel that was here (8 rows x 256 columns per workgroup, one column per thread):
-// bf16 8 x 4096 x 32003 1600 -> 61 us (262 MB of W at 4.3 TB/s), fp32 gated 512 x 1024 x 4096 186 -> 94 us (91 TFLOP/s),
-// fp32 8 x 256 x 512 31 us -> the launch.
+// bf16 8 x 4096 x 32003 1600 -> 54 us (262 MB of W at 4.9 TB/s), fp32 8 x 256 x 512 31 us -> the launch.
+// Of that, neighbouring column tiles on one XCD (xcd_run_tile): bf16 8 x 4096 x 32003 60.7 -> 54.0 us, fp32 1 x 4096 x 4096
+// (stripes of 64 bytes, two to a cache line) 21.2 -> 13.5 us, fp32 16 x 4096 x 11000 38.3 -> 30.6 us.
 //
 // What bounds it: 16 rows of 16-bit storage: streaming W (its fp32 products would keep up with 9.8 TB/s); more rows or
 // fp32 storage: the fp32 matrix rate, 256 operations per clock and compute unit (157 TFLOP/s).
@@ -57,7 +58,8 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane >> 4, c = lane & 15;
-    const int n0 = blockIdx.x * TN, m0 = blockIdx.y * (16 * RG);
+    const int tile = xcd_run_tile(blockIdx.x, gridDim.x);
+    const int n0 = tile * TN, m0 = blockIdx.y * (16 * RG);
     const bool gain = (flags & kFlagGain) != 0;
 
     const int nb = n0 + min(VW * c, N - VW - n0);  // this lane's first column (the host takes VW <= N)
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     const E* x_lane[RG];
 #pragma unroll
     for (int r = 0; r < RG; ++r) x_lane[r] = X + (size_t)min(m0 + 16 * r + c, M - 1) * K + XV * q;
-    const E* g_lane = gain ? g + XV * q : X;
+    const E* g_lane = (gain ? g : X) + XV * q;  // (without a gain the load is of no use, but it keeps the loop free of branches)
 
     f32x4 acc[G][RG][VW];
     float ss[RG];
@@ -82,7 +84,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
 
     auto load = [&](Blk& b, int kb) __attribute__((always_inline)) {
         const size_t k = (size_t)kb * KB;
-        if (gain) b.g.load(g_lane + k);
+        b.g.load(g_lane + k);
 #pragma unroll
         for (int r = 0; r < RG; ++r) b.x[r].load(x_lane[r] + k);
 #pragma unroll
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
 #pragma unroll
         for (int i = 0; i < XV; ++i) {
             const bool ok = k + XV * q + i < (size_t)K;
-            b.g.set(i, (ok && gain) ? g_lane[k + i] : S::narrow(0.f));
+            b.g.set(i, ok ? g_lane[k + i] : S::narrow(0.f));
 #pragma unroll
             for (int r = 0; r < RG; ++r) b.x[r].set(i, ok ? x_lane[r][k + i] : S::narrow(0.f));
 #pragma unroll
@@ -131,18 +133,23 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
         }
     };
 
-    // The next block is requested before the present one is multiplied.  (Two or four blocks a trip for the narrow tiles
-    // gain nothing: fp32 1 x 4096 x 4096 21.4 us with one, 23.5 us with four.)
+    // The next block is requested before the present one is multiplied: two named blocks in turn, and past the end the last
+    // one is asked for again.  A condition or a copy between a load and its use makes the compiler wait for the load there
+    // (fp32 64 x 4096 x 4096 30.2 -> 27.0 us without; three blocks: the same, bf16 8 x 4096 x 32003 8 % slower).
     const int nfull = K / KB;
-    {
-        Blk cur, next;
-        int kb = wave;
-        if (kb < nfull) load(cur, kb);
-        for (; kb < nfull; kb += nw) {
-            if (kb + nw < nfull) load(next, kb + nw);
+    if (wave < nfull) {
+        const int last = nfull - 1;
+        Blk even, odd;
+        load(even, wave);
+        for (int kb = wave;; kb += 2 * nw) {
+            load(odd, min(kb + nw, last));
             __builtin_amdgcn_sched_barrier(0);
-            multiply(cur);
-            cur = next;
+            multiply(even);
+            if (kb + nw > last) break;
+            load(even, min(kb + 2 * nw, last));
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(odd);
+            if (kb + 2 * nw > last) break;
         }
     }
     if (nfull * KB < K && wave == nfull % nw) {

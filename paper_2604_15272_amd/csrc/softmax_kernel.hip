@@ -328,16 +328,21 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
             }
         }
     };
+    // Two named blocks in turn, without a condition between a load and its use (general_kernel.hip).
     const int nfull = K / KBG;
-    {
-        Blk cur, next;
-        int kb = wave;
-        if (kb < nfull) load(cur, kb);
-        for (; kb < nfull; kb += nw) {
-            if (kb + nw < nfull) load(next, kb + nw);
+    if (wave < nfull) {
+        const int last = nfull - 1;
+        Blk even, odd;
+        load(even, wave);
+        for (int kb = wave;; kb += 2 * nw) {
+            load(odd, min(kb + nw, last));
             __builtin_amdgcn_sched_barrier(0);
-            multiply(cur);
-            cur = next;
+            multiply(even);
+            if (kb + nw > last) break;
+            load(even, min(kb + 2 * nw, last));
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(odd);
+            if (kb + 2 * nw > last) break;
         }
     }
     if (nfull * KBG < K && wave == nfull % nw) {

@@ -408,6 +408,13 @@ def test_decode_rows_with_x_through_lds_as_dispatched(P, dtype, M, K, N):
     _variant_case(P, dtype, M, K, N, "plain_nogain", seed=476)
 
 
+# Rows of W that are no multiple of 128 bytes, over 41 column tiles (five runs of neighbours and one left over) and 261.
+@pytest.mark.parametrize("M,K,N,gated", [(5, 264, 5128, False), (16, 520, 5128, True), (40, 264, 5128, False),
+                                         (33, 520, 5128, True), (8, 136, 33288, False)])
+def test_decode_ragged_row_pitch_in_runs_of_tiles(P, M, K, N, gated):
+    _case(P, pi.BF16, M, K, N, gated, seed=478, expect_path=P.PRISM_PATH_DECODE)
+
+
 def test_x_through_lds_is_refused_for_two_weight_matrices(P):
     P.prism_set_override(P.PRISM_PATH_DECODE, 0, 68)
     try:

@@ -33,8 +33,8 @@ constexpr int kRedFloats = NW * 16 * TN;  // one row group's partial tiles of al
 
 }  // namespace
 
-// XLDS (calls with one weight matrix): X reaches the wavefront through LDS (see the loop).
-template <typename F, bool GATED, int RG, bool XLDS>
+// XLDS (calls with one weight matrix): X reaches the wavefront through LDS (see the loop); STREAM there: one row block.
+template <typename F, bool GATED, int RG, bool XLDS, bool STREAM>
 __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ g,
                                                          const uint16_t* __restrict__ W1,
                                                          const uint16_t* __restrict__ W2, uint16_t* __restrict__ Y,
@@ -54,7 +54,8 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = lane >> 4, c = lane & 15;
-    const int ntile = blockIdx.x, split = blockIdx.y, rblock = blockIdx.z;
+    // (order of the tiles: as in the 16-row kernel; 100 x 4096 x 8008 36.2 -> 30.5 us, 40 x 4096 x 5000 16.6 -> 15.2 us)
+    const int ntile = tiles_share_lines(N, gridDim.x) ? xcd_run_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x, split = blockIdx.y, rblock = blockIdx.z;
     const int n_tiles = gridDim.x;
     const int n0 = ntile * TN, m0 = rblock * RB;
 
@@ -105,71 +106,98 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
     if constexpr (XLDS) {
         static_assert(!GATED, "calls with one weight matrix");
         // A load of X in MFMA operand layout (lane (q, c): row c, eight K values) touches sixteen rows for 64 bytes
-        // each, and the compute unit's memory path moves such loads at a third of the rate of loads that take 256
-        // contiguous bytes from each of four rows (measured: 17 against 57 bytes per clock).  So a wavefront takes
-        // four consecutive K-blocks at a time (128 K values = 256 bytes of a row) and moves their X into an LDS area
-        // of its own with buffer loads that have the LDS flag, four rows x 256 bytes per instruction; the operand
-        // is then read from LDS.  A load puts lane l's 16 bytes at l * 16 of its 1 KB group; lane l = 16 r + s of
-        // group j fetches the eight K values number s ^ (4 j + r) of row 4 j + r, so the sixteen rows of an operand
-        // read sit in sixteen different slots (no bank conflicts) and four consecutive lanes still fetch one aligned
-        // 64-byte piece.
+        // each, and the compute unit's memory path moves such loads at a third of the rate of loads that take at least 128
+        // contiguous bytes of a row (measured: 17 against 57 bytes per clock).  So a wavefront takes two consecutive
+        // K-blocks at a time (64 K values = 128 bytes of a row) and moves their X into an LDS area of its own with buffer
+        // loads that have the LDS flag, eight rows x 128 bytes per instruction; the operand is then read from LDS.  A load
+        // puts lane l's 16 bytes at l * 16 of its 1 KB group; lane l = 8 r + s of group j fetches the eight K values number
+        // s ^ r of row 8 j + r: the rows of an operand read then sit in different slots (no bank conflicts).
+        //
+        // Nothing waits for what it has just requested: the X of the next pair and the W of the next block are on their
+        // way while a block is multiplied (two areas per wavefront, two register sets of W).  The one wait that the
+        // compiler does not place, for X in LDS, counts instructions: only the youngest set of W (its eight rows and the
+        // gain) may still be in flight, and every group of loads is fenced so that it stays in the order written.
+        // Before (four blocks of X at a time, a full wait before each block) and now: 512 x 4096 x 4096 29.5 -> 27.0 us, 128 x
+        // 4096 x 4096 17.2 -> 15.2 us (as 32 rows), 200 x 4096 x 4096 23.2 -> 20.9 us.  What bounds it now: W and X through
+        // the L2, once per row block (18 TB/s over the chip at 200 x 4096 x 4096).
         typedef __attribute__((address_space(3))) void* lds_ptr;
-        u32x4* xs_lane = (u32x4*)lds + (size_t)wave * (RG * 256);
-        u32x4* xs_uni = (u32x4*)lds + (size_t)__builtin_amdgcn_readfirstlane(wave) * (RG * 256);
-        const int r4 = lane >> 4, slot = lane & 15;
-        const int nsb = (b_cnt + 3) / 4;  // super-blocks of four K-blocks in this slice
+        constexpr int AREA = RG * 128;  // 16-byte slots of a pair's X
+        u32x4* xs_lane = (u32x4*)lds + (size_t)wave * (2 * AREA);
+        u32x4* xs_uni = (u32x4*)lds + (size_t)__builtin_amdgcn_readfirstlane(wave) * (2 * AREA);
+        const int r8 = lane >> 3, oct = (lane & 7) ^ (lane >> 3);
+        const int npairs = (b_cnt + 1) / 2;
         const bool gain = (flags & kFlagGain) != 0;
-        for (int sb = lwave; sb < nsb; sb += LNW) {
+        auto request_x = [&](int area, int p) __attribute__((always_inline)) {
+            const int ib = 2 * p + (oct >> 2);
+            const int k = (b_beg + 2 * p) * KB + 8 * oct;
+            const bool k_ok = (p < npairs) & (ib < b_cnt) & (k < K);
 #pragma unroll
-            for (int r = 0; r < RG; ++r) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int row = 16 * r + 4 * j + r4;          // of this workgroup's rows
-                    const int oct = slot ^ (4 * j + r4);          // eight K values number oct of the super-block
-                    const int ib = 4 * sb + (oct >> 2);
-                    const int k = (b_beg + 4 * sb) * KB + 8 * oct;
-                    const bool ok = (ib < b_cnt) & (k < K) & (m0 + row < M);
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr)(xs_uni + (r * 4 + j) * 64), 16,
-                                                             (int)(ok ? (u32)row * (u32)K * 2u + (u32)k * 2u : kOutOfRange), 0, 0, 0);
-                }
+            for (int j = 0; j < 2 * RG; ++j) {
+                const int row = 8 * j + r8;  // of this workgroup's rows
+                const bool ok = k_ok & (m0 + row < M);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr)(xs_uni + area * AREA + j * 64), 16,
+                                                         (int)(ok ? (u32)row * (u32)K * 2u + (u32)k * 2u : kOutOfRange), 0, 0, 0);
             }
-            // One block at a time (not unrolled: unrolled, the compiler requests all four blocks' W at once and
-            // runs out of registers; a second W set in flight under the products was measured and gains nothing).
-#pragma unroll 1
-            for (int bb = 0; bb < 4; ++bb) {
-                const int ib = 4 * sb + bb;
-                const bool has = ib < b_cnt;
-                const u32 woff = has ? w_lane + (u32)ib * KB * row_bytes : kOutOfRange;
-                const int k = (b_beg + ib) * KB + 8 * q;
-                WRows w1;
-                u32x4 xr[RG];
-                const u32x4 gl = load16(rg, (gain & has & (k < K)) ? (u32)k * 2u : kOutOfRange);
-                if (stream_w) load_w_block<true>(w1, rw1, woff, row_bytes);
-                else load_w_block<false>(w1, rw1, woff, row_bytes);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this super-block's X is in LDS (and W in registers)
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        WRows w[2];
+        u32x4 gl[2];
+        auto load_wg = [&](auto set_c, int ib) __attribute__((always_inline)) {
+            constexpr int SET = decltype(set_c)::value;
+            const bool has = ib < b_cnt;
+            const u32 woff = has ? w_lane + (u32)ib * KB * row_bytes : kOutOfRange;
+            const int k = (b_beg + ib) * KB + 8 * q;
+            // (without a gain tensor the load is out of range and fetches nothing: the wait below counts it)
+            gl[SET] = load16(rg, (gain & has & (k < K)) ? (u32)k * 2u : kOutOfRange);
+            load_w_block<STREAM>(w[SET], rw1, woff, row_bytes);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        u32x4 xr[RG];
+        auto read_x = [&](int area, int bb) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < RG; ++r)
-                    xr[r] = xs_lane[r * 256 + (c >> 2) * 64 + (c & 3) * 16 + (((4 * bb + q) ^ c) & 15)];
-                const u32x4 gr = gain ? gl : ones8<F>();
-                u32x4 a[RG];
+            for (int r = 0; r < RG; ++r)
+                xr[r] = xs_lane[area * AREA + (2 * r + (c >> 3)) * 64 + (c & 7) * 8 + ((4 * bb + q) ^ (c & 7))];
+        };
+        auto products = [&](auto set_c) __attribute__((always_inline)) {
+            constexpr int SET = decltype(set_c)::value;
+            const u32x4 gr = gain ? gl[SET] : ones8<F>();
+            u32x4 a[RG];
 #pragma unroll
-                for (int r = 0; r < RG; ++r) a[r] = scaled_a_operand<F>(xr[r], gr, ss[r]);
-                auto step = [&](auto jc) __attribute__((always_inline)) {
-                    constexpr int J = decltype(jc)::value;
-                    const u32x4 b1 = b_operand<J>(w1);
+            for (int r = 0; r < RG; ++r) a[r] = scaled_a_operand<F>(xr[r], gr, ss[r]);
+            auto step = [&](auto jc) __attribute__((always_inline)) {
+                constexpr int J = decltype(jc)::value;
+                const u32x4 b1 = b_operand<J>(w[SET]);
 #pragma unroll
-                    for (int r = 0; r < RG; ++r) acc1[r][J] = F::mfma_16x16x32(a[r], b1, acc1[r][J]);
-                };
-                step(std::integral_constant<int, 0>{});
-                step(std::integral_constant<int, 1>{});
-                step(std::integral_constant<int, 2>{});
-                step(std::integral_constant<int, 3>{});
-                step(std::integral_constant<int, 4>{});
-                step(std::integral_constant<int, 5>{});
-                step(std::integral_constant<int, 6>{});
-                step(std::integral_constant<int, 7>{});
-            }
+                for (int r = 0; r < RG; ++r) acc1[r][J] = F::mfma_16x16x32(a[r], b1, acc1[r][J]);
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+            step(std::integral_constant<int, 4>{});
+            step(std::integral_constant<int, 5>{});
+            step(std::integral_constant<int, 6>{});
+            step(std::integral_constant<int, 7>{});
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const std::integral_constant<int, 0> set0{};
+        const std::integral_constant<int, 1> set1{};
+        request_x(0, lwave);
+        load_wg(set0, 2 * lwave);
+        int area = 0;
+        for (int p = lwave; p < npairs; p += LNW) {
+            load_wg(set1, 2 * p + 1);
+            asm volatile("s_waitcnt vmcnt(9)" ::: "memory");  // this pair's X is in LDS
+            __builtin_amdgcn_sched_barrier(0);
+            read_x(area, 0);
+            request_x(area ^ 1, p + LNW);  // (the other area was last read for products that are done)
+            products(set0);
+            load_wg(set0, 2 * (p + LNW));
+            read_x(area, 1);
+            products(set1);
+            area ^= 1;
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // requests past the last pair still write (zeros) to LDS
         __syncthreads();  // the areas are reused by the reduction below
     } else {
         // U K-blocks per trip: sixteen 16-byte row loads of W in flight per lane where the registers allow it.
@@ -380,13 +408,13 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
     }
 }
 
-template <typename F, bool GATED, int RG, bool XLDS>
+template <typename F, bool GATED, int RG, bool XLDS, bool STREAM = false>
 static hipError_t launch_rows(const Call& c, int S, const DecodeWorkspace& ws) {
     const int n_tiles = (c.N + TN - 1) / TN;
     const int row_blocks = (c.M + 16 * RG - 1) / (16 * RG);
     dim3 grid(n_tiles, S, row_blocks), block(NT);
     const size_t lds = (size_t)(2 * kRedFloats + NW * 16 * RG) * sizeof(float);
-    auto kern = decode_rows_kernel<F, GATED, RG, XLDS>;
+    auto kern = decode_rows_kernel<F, GATED, RG, XLDS, STREAM>;
     static std::atomic<uint64_t> opted{0};
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, c.stream, (const uint16_t*)c.X, (const uint16_t*)c.g,
@@ -397,13 +425,17 @@ static hipError_t launch_rows(const Call& c, int S, const DecodeWorkspace& ws) {
 
 template <typename F>
 static hipError_t launch_rows_fmt(const Call& c, int split_k, int row_groups, bool xlds, const DecodeWorkspace& ws) {
+    const bool stream = c.M <= 16 * row_groups;  // one row block: W is read by one workgroup per slice
     if (c.gated) {
         if (xlds) return hipErrorInvalidValue;
         if (row_groups == 2) return launch_rows<F, true, 2, false>(c, split_k, ws);
         if (row_groups == 4) return launch_rows<F, true, 4, false>(c, split_k, ws);
+    } else if (xlds) {
+        if (row_groups == 2) return stream ? launch_rows<F, false, 2, true, true>(c, split_k, ws) : launch_rows<F, false, 2, true>(c, split_k, ws);
+        if (row_groups == 4) return stream ? launch_rows<F, false, 4, true, true>(c, split_k, ws) : launch_rows<F, false, 4, true>(c, split_k, ws);
     } else {
-        if (row_groups == 2) return xlds ? launch_rows<F, false, 2, true>(c, split_k, ws) : launch_rows<F, false, 2, false>(c, split_k, ws);
-        if (row_groups == 4) return xlds ? launch_rows<F, false, 4, true>(c, split_k, ws) : launch_rows<F, false, 4, false>(c, split_k, ws);
+        if (row_groups == 2) return launch_rows<F, false, 2, false>(c, split_k, ws);
+        if (row_groups == 4) return launch_rows<F, false, 4, false>(c, split_k, ws);
     }
     return hipErrorInvalidValue;
 }

@@ -184,11 +184,14 @@ void choose_prefill_tile(bool gated, int64_t M, int64_t N, int variant, int* bm,
 // HBM terms and the second-round factor come from: 0.2 % on average, 16 % at worst (2.4 % / 40 % for gated calls
 // before them).
 //   multi-row kernel, RG row groups, S K-slices, z row blocks, all times in microseconds:
-//     loop      = ceil(kblocks / S) x c x rounds (x 1.1 from the second round on),  c = 0.22 / 0.31 per K-block for
-//                 32 / 64 rows of one matrix, 0.33 / 0.60 for two (per compute unit a K-block costs its MFMAs, its
-//                 vector work and 8 to 12 KiB through the L1, and they do not overlap); rounds = ceil(workgroups /
-//                 compute units);
-//                 never less than streaming W at 6 TB/s: once, or once per row block when W is beyond 128 MB
+//     loop      = ceil(kblocks / S) x c x rounds (x 1.3 from the second round on, x 1.1 for two matrices),  c = 0.13 /
+//                 0.19 per K-block for 32 / 64 rows of one matrix, 0.33 / 0.60 for two (there a K-block's MFMAs, vector work
+//                 and 8 to 12 KiB through the L1 do not overlap); rounds = ceil(workgroups / compute units);
+//                 never less than streaming W at 5 / 6 TB/s (one / two matrices): once and 0.3 of that for every further
+//                 row block (one matrix), or once per row block when W is beyond 128 MB
+//   The constants of one matrix are of the pipelined loop (decode_rows_kernel.hip): 110 calls of 17 to 512 rows against
+//   eleven K x N from 512 x 3072 to 14336 x 4096, weights rotated through HBM: 0.9 % above the best of the candidates on
+//   average, 14 % at worst (8192 x 8192, 384 rows), none more than 1.7 % slower than with the constants before.
 //     reduction = 0.5 x RG x matrices (LDS)
 //     exchange  = 2.5 + S x RG x matrices / 8 when S > 1 (three dependent round trips, then the last arrival
 //                 pulls S partial tiles through one compute unit)
@@ -207,14 +210,16 @@ RowsEstimate rows_estimate(int rg, bool gated, int64_t M, int64_t K, int64_t N, 
     const int64_t z = (M + 16 * rg - 1) / (16 * rg), wgs1 = n_tiles * z;
     int64_t S = wgs1 <= cus ? cus / wgs1 : 1;
     S = std::max<int64_t>(1, std::min<int64_t>(S, std::max<int64_t>(1, kblocks / 8)));
-    const double c = gated ? (rg == 2 ? 0.33 : 0.60) : (rg == 2 ? 0.22 : 0.31);
+    const double c = gated ? (rg == 2 ? 0.33 : 0.60) : (rg == 2 ? 0.13 : 0.19);
     const int64_t rounds = (wgs1 * S + cus - 1) / cus;
-    double loop = (double)((kblocks + S - 1) / S) * c * (double)rounds * (rounds >= 2 ? 1.1 : 1.0);
+    double loop = (double)((kblocks + S - 1) / S) * c * (double)rounds * (rounds >= 2 ? (gated ? 1.1 : 1.3) : 1.0);
     // Never faster than W streams from HBM; weights too large for the last-level cache to keep between the row
     // blocks of a tile (256 MB; 128 MB taken) stream once per row block (gated 4096 x 14336, 48 rows as 2 x 32:
-    // 58.7 us against 47.3 us for 32 rows; 8192 x 28672: 321 against 156 us).
+    // 58.7 us against 47.3 us for 32 rows; 8192 x 28672: 321 against 156 us), smaller ones still cost a part of that (one
+    // matrix, 4096 x 14336, 48 rows: 32.2 us as 2 x 32, 28.2 us as 1 x 64).
     const double w_bytes = 2.0 * (double)K * (double)N * G;
-    loop = std::max(loop, w_bytes / 6.0e6 * (w_bytes > 128.0e6 ? (double)z : 1.0));
+    const double reads = w_bytes > 128.0e6 ? (double)z : (gated ? 1.0 : 1.0 + 0.3 * (double)(z - 1));
+    loop = std::max(loop, w_bytes / (gated ? 6.0e6 : 5.0e6) * reads);
     double us = loop + 0.5 * rg * G + 1.5;
     if (S > 1) us += 2.5 + (double)(S * rg * G) / 8.0;
     return RowsEstimate{us, S};
@@ -510,8 +515,7 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
             row_groups = decode_row_groups(gated, M, K, N);
             if (row_groups == 0) row_groups = 4;  // forced onto a shape the heuristic leaves to prefill
             // Variants 32 / 64: rows per workgroup, X loaded straight into operand registers; 36 / 68 (one weight
-            // matrix only): the same with X through LDS (wide loads of four K-blocks at a time).  Not forced: the
-            // second form where a slice gives every wavefront at least two of those super-blocks.
+            // matrix only): the same with X through LDS (wide loads of two K-blocks at a time, requested ahead).
             if (variant == 32 || variant == 64) row_groups = variant / 16;
             else if (variant == 36 || variant == 68) {
                 if (gated) return PRISM_ERR_UNSUPPORTED;
@@ -680,12 +684,14 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
                 }
             }
         }
-        // Measured (us, X through LDS against straight loads): 512 x 4096 x 4096 32.1 / 34.1, 256 x 14336 x 4096
-        // 56.6 / 65.5, 1024 x 4096 x 6144 85.4 / 92.7; with slices of 16 K-blocks (64 x 4096 x 4096) 18.3 / 16.7.
-        // A single row block whose row groups are less than three quarters full moves padding through LDS for nothing
-        // (17 rows in a 32-row workgroup: 2 to 7 % slower on five shapes; 24 of 32 and 48 of 64: even).
-        if (row_groups > 1 && !gated && variant == 0 && kblocks / std::max<int64_t>(1, S) >= 64 &&
-            (row_blocks > 1 || M * 4 >= 3 * 16 * row_groups))
+        // X through LDS or straight loads (one matrix; us, LDS / straight).  32 rows per workgroup: LDS, except a single row
+        // block in slices of 9 to 31 K-blocks, where W streams and few wavefronts have a next block to fetch (128 x 4096 x
+        // 4096 15.4 / 17.2, 32 x 8192 x 8192 27.8 / 29.0, 32 x 1024 x 4096, eight K-blocks, 9.0 / 9.9; but 17 x 4096 x 4096,
+        // sixteen K-blocks, 13.0 / 12.1).  64 rows: LDS from 48 K-blocks a slice (512 x 4096 x 4096 28.1 / 32.2, 64 x 14336 x
+        // 4096 30.2 / 31.9; but 128 x 4096 x 4096, 32 K-blocks, 17.5 / 17.2, 48 x 4096 x 6144, 26 K-blocks, 20.1 / 18.6).
+        const int64_t slice_blocks = (kblocks + S - 1) / std::max<int64_t>(1, S);
+        if (row_groups > 1 && !gated && variant == 0 &&
+            (row_groups == 2 ? (row_blocks > 1 || slice_blocks >= 32 || slice_blocks <= 8) : slice_blocks >= 48))
             xlds = true;
         out->waves = waves;
         out->row_groups = row_groups;

@@ -327,12 +327,12 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(const uint16_t* __restr
         // Workgroups start in the order of their numbers.  With sp.slow set (bit j: column tiles j, j + 8, ... lie in
         // address units that stream slowly; the tile count is a multiple of 8) those tiles get the first numbers: in
         // a launch of several rounds the workgroups that start last then are not the ones that take longest.
-        // Neighbouring tiles on one XCD where they share cache lines (rows of W that are no multiple of 128 bytes): 8 x 4096 x
-        // 32008 55.3 -> 44.8 us, gated 4 x 4096 x 8008 31.0 -> 27.0 us, 8 x 4096 x 5000 (40 tiles) 12.4 -> 11.5 us.  Where
-        // they don't, the plain order is the faster one (16 x 4096 x 4096 8.5 us, 9.4 us in runs), and with few tiles there
-        // are no runs to speak of (gated 16 x 2048 x 4104, 33 tiles: 14.0 us, 14.5 us in runs).
-        int tile = tiles_share_lines(N, gridDim.x) ? xcd_run_tile(blockIdx.x, gridDim.x) : blockIdx.x;
-        if (sp.slow != 0) {
+        int tile = blockIdx.x;
+        // sp.period = kTileRuns: neighbouring tiles on one XCD, where they share cache lines (the host says when).  (The host and
+        // not the kernel looks at that, because asking for the grid's size on every call costs the others 0.25 us.)
+        if (sp.slow != 0 && sp.period == kTileRuns) {
+            tile = xcd_run_tile(blockIdx.x, gridDim.x);
+        } else if (sp.slow != 0) {
             const uint32_t c_slow = (uint32_t)__builtin_popcount(sp.slow & 0xFFu), n_slow = (gridDim.x >> 3) * c_slow;
             uint32_t pos = blockIdx.x, mask = sp.slow & 0xFFu, c = c_slow;
             if (pos >= n_slow) {

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane >> 4, c = lane & 15;
-    const int tile = xcd_run_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_run_tile(blockIdx.x, (unsigned)((N + TN - 1) / TN));  // (gridDim.x would be one more load to wait for)
     const int n0 = tile * TN, m0 = blockIdx.y * (16 * RG);
     const bool gain = (flags & kFlagGain) != 0;
 

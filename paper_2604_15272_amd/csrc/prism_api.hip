@@ -876,6 +876,15 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
                 }
             }
             if (plan.row_groups == 1 && sp.G == 0) sp = slow_tiles_first(W1, gated ? W2 : nullptr, N, plan.pub.grid_x, split, plan.packed);
+            // Neighbouring tiles on one XCD where they share cache lines (rows of W that are no multiple of 128 bytes): 8 x
+            // 4096 x 32008 55.3 -> 44.8 us, gated 4 x 4096 x 8008 31.0 -> 27.0 us, 8 x 4096 x 5000 (40 tiles) 12.4 -> 11.5 us.
+            // Where they don't, the plain order is the faster one (16 x 4096 x 4096 8.5 us, 9.4 us in runs), and with few
+            // tiles there are no runs to speak of (gated 16 x 2048 x 4104, 33 tiles: 14.0 us, 14.5 us in runs).
+            if (plan.row_groups == 1 && sp.G == 0 && (N & 63) != 0 && plan.pub.grid_x >= 40) {
+                sp = StreamPartition{};
+                sp.slow = 1;
+                sp.period = kTileRuns;
+            }
             err = plan.row_groups > 1
                       ? launch_decode_rows_16bit(c, dtype == PRISM_F16, plan.pub.split_k, plan.row_groups, plan.xlds, ws)
                       : launch_decode_16bit(c, dtype == PRISM_F16, split, sp, plan.waves, plan.packed, ws);

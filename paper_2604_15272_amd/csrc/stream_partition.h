@@ -27,6 +27,9 @@ struct StreamPartition {
     uint32_t q, r;     // T = q * G + r
 };
 
+// In `period` of a plain grid (G = 0): column tiles in runs of neighbours, one run per XCD.
+constexpr uint32_t kTileRuns = 1;
+
 constexpr uint32_t kStreamMaxSlices = 32;  // partial sums per tile the kernel can count (half a wavefront)
 
 __host__ __device__ inline uint32_t sp_weight(const StreamPartition& p, uint32_t t) {

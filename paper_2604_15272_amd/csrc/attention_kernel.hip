@@ -26,7 +26,8 @@
 // Everything is tiny at the paper's sizes (1 - 2 MiB of keys and values in all): the kernel is bound
 // by its chain of dependent steps, not by bandwidth.
 //
-// Plain kernel: any head dimension up to 1024, any G, any storage type; one workgroup per (head,
+// fp32 storage, head dimension 64, more than 16 heads: attention_general_kernel.hip.
+// Plain kernel: the other head dimensions up to 1024, any G, any storage type; one workgroup per (head,
 // batch entry), keys in chunks of 256 with a running maximum.
 #include <type_traits>
 
@@ -431,6 +432,7 @@ static hipError_t launch_gqa_simple_t(const AttentionCall& c) {
 }
 
 hipError_t launch_gqa_simple(const AttentionCall& c, int dtype) {
+    if (c.D == 64 || c.D == 128) return launch_gqa_general(c, dtype);
     if (dtype == PRISM_F32) return launch_gqa_simple_t<float>(c);
     if (dtype == PRISM_F16) return launch_gqa_simple_t<_Float16>(c);
     return launch_gqa_simple_t<uint16_t>(c);

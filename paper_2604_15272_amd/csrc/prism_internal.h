@@ -144,5 +144,6 @@ hipError_t launch_probe_mfma(float* sink, int workgroups, int iters, hipStream_t
 hipError_t launch_softmax_simple(const SoftmaxCall& c, int dtype);
 hipError_t launch_gqa_16bit(const AttentionCall& c, bool f16, const AttentionPlan& p, const AttentionWorkspace& ws);
 hipError_t launch_gqa_simple(const AttentionCall& c, int dtype);
+hipError_t launch_gqa_general(const AttentionCall& c, int dtype);
 
 }  // namespace prism

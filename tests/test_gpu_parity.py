@@ -393,8 +393,8 @@ def test_decode_rows_every_split_and_row_count(P, split, rows, gated):
 @pytest.mark.parametrize("rows", [36, 68])
 @pytest.mark.parametrize("split", [1, 2, 3, 7, 16, 33])
 def test_decode_rows_with_x_through_lds_every_split_and_row_count(P, split, rows):
-    """The same for the loop that moves X through LDS four K-blocks at a time (variants 36 / 68): slices that are
-    no multiple of four K-blocks, slices shorter than a wavefront's share, ragged K, N and M."""
+    """The same for the loop that moves X through LDS two K-blocks at a time (variants 36 / 68): slices that are
+    no multiple of two K-blocks, slices shorter than a wavefront's share, ragged K, N and M."""
     _case(P, pi.BF16, 75, 2056, 1160, False, seed=470, path=P.PRISM_PATH_DECODE, split=split, variant=rows)
 
 
@@ -819,6 +819,33 @@ def test_attention_single_slice(P):
 def test_attention_plain_kernel(P, dtype, B, G, H, D, qk_norm):
     _attention_case(P, dtype, B, G, H, D, seed=1420 + H, scale=128.0 ** 0.5 / D ** 0.5, qk_norm=qk_norm,
                     expect_path=P.PRISM_PATH_SIMPLE)
+
+
+# The fp32 matrix-core kernel: fewer keys than a block of 16, whole blocks, a rest; fewer and more blocks than wavefronts; one
+# head, a full group of 16 and a second group.
+@pytest.mark.parametrize("dtype,D", [(pi.F32, 64), (pi.F32, 128), (pi.BF16, 64), (pi.F16, 64)])
+@pytest.mark.parametrize("B,G,H,qk_norm", [(1, 1, 1, False), (3, 8, 15, True), (2, 16, 16, False), (2, 17, 250, True),
+                                           (1, 5, 128, False), (2, 8, 2005, True)])
+def test_attention_fp32_matrix_core_kernel(P, dtype, D, B, G, H, qk_norm):
+    _attention_case(P, dtype, B, G, H, D, seed=770 + H, scale=D ** -0.5, qk_norm=qk_norm, expect_path=P.PRISM_PATH_SIMPLE)
+
+
+@pytest.mark.parametrize("dtype", [pi.BF16, pi.F16])
+def test_attention_more_heads_than_the_16_bit_kernel_takes(P, dtype):
+    _attention_case(P, dtype, 2, 40, 333, 128, seed=790, scale=128 ** -0.5, expect_path=P.PRISM_PATH_SIMPLE)
+
+
+def test_attention_fp32_kernel_keeps_infinities_in_v_past_the_end_out(P):
+    """Keys of the next batch entry, with infinities, lie right behind a last block that is not full."""
+    import torch
+    gen = torch.Generator().manual_seed(7)
+    Q, K, V = torch.randn(2, 4, 64, generator=gen), torch.randn(2, 21, 64, generator=gen), torch.randn(2, 21, 64, generator=gen)
+    V[1, :12] = float("inf")
+    O = torch.empty_like(Q).cuda()
+    P.prism_gqa_decode_attention(Q.cuda(), K.cuda(), V.cuda(), O, scale=0.125)
+    ref = torch.softmax(Q[0].double() @ K[0].double().T * 0.125, -1) @ V[0].double()
+    torch.testing.assert_close(O[0].double().cpu(), ref, rtol=1e-5, atol=1e-5)
+    assert bool(torch.isinf(O[1]).all())
 
 
 def test_attention_scale_and_sign(P):

@@ -115,6 +115,47 @@ def _load():
 
 lib = _load()
 
+PRISM_ERR_WORKSPACE = 3
+
+
+def _load_marshal():
+    """The native route of ordinary calls (csrc/marshal.cpp); None where there is no torch to take tensors from."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    from . import _marshal
+    _marshal.setup(torch.Tensor, torch.nn.Parameter, torch.float32, torch.bfloat16, torch.float16,
+                   getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+    return _marshal
+
+
+_native = _load_marshal()
+
+
+def _address_of(fn):
+    return ctypes.cast(fn, ctypes.c_void_p).value
+
+
+# The C entry points and which arguments they take, as csrc/marshal.cpp counts them.
+_MATMUL = (_address_of(lib.prism_rmsnorm_matmul), 0)
+_MATMUL_STATIC = (_address_of(lib.prism_rmsnorm_matmul_static), 0)
+_GATED_MLP = (_address_of(lib.prism_rmsnorm_gated_mlp), 1)
+_GLU = (_address_of(lib.prism_rmsnorm_glu), 1)
+_SWIGLU = (_address_of(lib.prism_swiglu), 2)
+_SOFTMAX = (_address_of(lib.prism_softmax_matmul), 3)
+_ATTENTION = _address_of(lib.prism_gqa_decode_attention)
+
+
+def _done(st, what):
+    """Whether the native route has made the call.  One that lacks workspace has launched nothing: the general route
+    registers the workspace and makes the call."""
+    if st is None or st == PRISM_ERR_WORKSPACE:
+        return False
+    if st != 0:
+        raise PrismError(st, what)
+    return True
+
 
 def prism_status_string(status):
     return lib.prism_status_string(int(status)).decode()
@@ -251,6 +292,9 @@ def ensure_workspace(nbytes, device=None):
 
 def prism_rmsnorm_matmul(X, g, W, Y, M=None, K=None, N=None, eps=1e-6, dtype=None, stream=None):
     """Y[M,N] = rms_norm(X; g, eps) @ W on the GPU.  Tensors are torch CUDA tensors or addresses."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_MATMUL, X, g, W, None, Y, eps), "prism_rmsnorm_matmul"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W.shape[1]
@@ -270,6 +314,9 @@ PROBE_LOADS_BYTES = 1048576   # PRISM_PROBE_LOADS_BYTES: what prism_probe_loads 
 
 def prism_rmsnorm_matmul_static(X, g, W, Y, M=None, K=None, N=None, eps=1e-6, dtype=None, stream=None):
     """prism_rmsnorm_matmul through the library's own static device scratch: registers and allocates nothing."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_MATMUL_STATIC, X, g, W, None, Y, eps), "prism_rmsnorm_matmul_static"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W.shape[1]
@@ -282,6 +329,9 @@ def prism_rmsnorm_matmul_static(X, g, W, Y, M=None, K=None, N=None, eps=1e-6, dt
 
 def prism_rmsnorm_gated_mlp(X, g, W1, W2, Y, M=None, K=None, N=None, eps=1e-6, dtype=None, stream=None):
     """Y[M,N] = silu(Nrm @ W1) * (Nrm @ W2), Nrm = rms_norm(X; g, eps), on the GPU."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_GATED_MLP, X, g, W1, W2, Y, eps), "prism_rmsnorm_gated_mlp"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W1.shape[1]
@@ -297,6 +347,9 @@ def prism_rmsnorm_gated_mlp(X, g, W1, W2, Y, M=None, K=None, N=None, eps=1e-6, d
 
 def prism_rmsnorm_glu(X, g, W1, W2, Y, M=None, K=None, N=None, eps=1e-6, dtype=None, stream=None):
     """Y[M,N] = (Nrm @ W1) * (Nrm @ W2), Nrm = rms_norm(X; g, eps): the paper's RMSNorm-MLP (no activation)."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_GLU, X, g, W1, W2, Y, eps), "prism_rmsnorm_glu"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W1.shape[1]
@@ -312,6 +365,9 @@ def prism_rmsnorm_glu(X, g, W1, W2, Y, M=None, K=None, N=None, eps=1e-6, dtype=N
 
 def prism_swiglu(X, W_gate, W_up, Y, M=None, K=None, N=None, dtype=None, stream=None):
     """Y[M,N] = silu(X @ W_gate) * (X @ W_up): the paper's SwiGLU (no normalisation, no gain)."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_SWIGLU, X, None, W_gate, W_up, Y, 0.0), "prism_swiglu"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W_gate.shape[1]
@@ -327,6 +383,9 @@ def prism_swiglu(X, W_gate, W_up, Y, M=None, K=None, N=None, dtype=None, stream=
 
 def prism_softmax_matmul(X, W, Y, M=None, K=None, N=None, dtype=None, stream=None):
     """Y[M,N] = softmax(X, over k) @ W: the paper's running example (Figure 1)."""
+    if M is None and dtype is None and stream is None and _native is not None:
+        if _done(_native.product(*_SOFTMAX, X, None, W, None, Y, 0.0), "prism_softmax_matmul"):
+            return Y
     if M is None:
         M, K = X.shape
         N = W.shape[1]
@@ -349,6 +408,9 @@ def prism_attention_plan(B, G, H, D, dtype):
 
 def prism_gqa_decode_attention(Q, K, V, O, scale=1.0, qk_norm=False, eps=1e-6, dtype=None, stream=None):
     """O[B,G,D] = softmax(scale * Qn @ K^T) @ V per batch entry (Q [B,G,D]; K, V [B,H,D]); Qn = rms_norm(Q) if qk_norm."""
+    if dtype is None and stream is None and _native is not None:
+        if _done(_native.attention(_ATTENTION, Q, K, V, O, scale, qk_norm, eps), "prism_gqa_decode_attention"):
+            return O
     B, G, D = Q.shape
     H = K.shape[1]
     dt = _dtype_of(Q, dtype)

@@ -1,12 +1,15 @@
-"""Compile the HIP sources into ``libprism.so`` next to this file (gfx950 only)."""
+"""Compile the HIP sources into ``libprism.so`` (gfx950 only) and the marshalling of Python calls into ``_marshal.so``,
+both next to this file."""
 import glob
 import os
 import shutil
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libprism.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 # Packed-fp32 instructions are switched off for every HIP translation unit.
 HIPCC_FLAGS = [
@@ -27,8 +30,21 @@ def sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 
 
+def build_marshal():
+    """The Python extension module of ``csrc/marshal.cpp`` (host code; it is handed the library's addresses at run time)."""
+    cmd = [os.environ.get("CXX") or shutil.which("g++") or shutil.which("amdclang++") or "c++", "-O2", "-std=c++17", "-shared",
+           "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"], os.path.join(HERE, "csrc", "marshal.cpp"), "-o",
+           MARSHAL + ".tmp"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("compiling marshal.cpp failed:\n" + " ".join(cmd) + "\n" + res.stderr)
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    return MARSHAL
+
+
 def build_library(verbose=False):
     """Always recompiles; raises on any compiler error."""
+    build_marshal()
     cmd = [hipcc_path()] + [f for f in HIPCC_FLAGS if f] + [
         "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
     ] + sources() + ["-o", LIB + ".tmp"]

@@ -1,0 +1,177 @@
+// The ordinary call from Python: torch tensors in, one C-ABI call out.
+//
+// binding.py's general route (ctypes, a workspace query before each call, the current stream through torch.cuda) takes
+// longer than the small calls it makes.  This module takes the calls in which every tensor is a plain
+// torch.Tensor (or Parameter), sizes and type are the tensors' own, X is on the GPU and no stream is named; it returns the library's status, or None
+// for a call that is not of that kind or that Python refuses somewhere on the way: the general route then
+// takes it from the start and raises what it always raised.  Tensors are looked at through their Python attributes, on every
+// call.  Time per call (fp32 X[8,256] . W[256,512], 3.1 us on the GPU,
+// call after call): 9.3 us on the general route, 5.1 us on this one.
+// A call that names its stream keeps the general route: programs that hand tensors from one stream to another with nothing
+// but host time between them are wrong, but they are left as they were.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <stdint.h>
+
+namespace {
+
+PyObject *t_tensor, *t_parameter, *dt_f32, *dt_bf16, *dt_f16, *f_device, *f_stream;
+PyObject *s_shape, *s_dtype, *s_is_cuda, *s_is_contiguous, *s_data_ptr;
+
+typedef int32_t (*ProductFn)(const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, float, int32_t, void*);
+typedef int32_t (*GatedFn)(const void*, const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, float, int32_t,
+                           void*);
+typedef int32_t (*SwigluFn)(const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, int32_t, void*);
+typedef int32_t (*SoftmaxFn)(const void*, const void*, void*, int64_t, int64_t, int64_t, int32_t, void*);
+typedef int32_t (*AttentionFn)(const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, int64_t, float, int32_t,
+                               float, int32_t, void*);
+
+// Which arguments a member of the family has.
+enum Kind { kProduct, kGated, kSwiglu, kSoftmax };
+
+PyObject* not_mine() {
+    PyErr_Clear();
+    Py_RETURN_NONE;
+}
+
+// Address of a contiguous plain tensor; None is a null pointer where that is allowed.
+bool address(PyObject* t, bool optional, void** out) {
+    if (t == Py_None && optional) {
+        *out = nullptr;
+        return true;
+    }
+    if ((PyObject*)Py_TYPE(t) != t_tensor && (PyObject*)Py_TYPE(t) != t_parameter) return false;
+    PyObject* c = PyObject_CallMethodNoArgs(t, s_is_contiguous);
+    if (!c) return false;
+    const bool contiguous = c == Py_True;
+    Py_DECREF(c);
+    if (!contiguous) return false;
+    PyObject* p = PyObject_CallMethodNoArgs(t, s_data_ptr);
+    if (!p) return false;
+    *out = PyLong_AsVoidPtr(p);
+    Py_DECREF(p);
+    return !PyErr_Occurred();
+}
+
+// Sizes of a tensor, which must have `dims` of them (at least that many if `more`).
+bool sizes(PyObject* t, Py_ssize_t dims, bool more, int64_t* out) {
+    PyObject* s = PyObject_GetAttr(t, s_shape);
+    if (!s) return false;
+    bool ok = PyTuple_Check(s) && (PyTuple_GET_SIZE(s) == dims || (more && PyTuple_GET_SIZE(s) > dims));
+    for (Py_ssize_t i = 0; ok && i < dims; ++i) {
+        PyObject* v = PyTuple_GET_ITEM(s, i);
+        ok = PyLong_CheckExact(v);
+        if (ok) out[i] = PyLong_AsLongLong(v);
+    }
+    Py_DECREF(s);
+    return ok && !PyErr_Occurred();
+}
+
+bool storage_type(PyObject* t, int32_t* out) {
+    PyObject* d = PyObject_GetAttr(t, s_dtype);
+    if (!d) return false;
+    *out = d == dt_f32 ? 0 : d == dt_bf16 ? 1 : d == dt_f16 ? 2 : -1;
+    Py_DECREF(d);
+    return *out >= 0;
+}
+
+bool on_gpu(PyObject* t) {
+    PyObject* v = PyObject_GetAttr(t, s_is_cuda);
+    const bool yes = v == Py_True;
+    Py_XDECREF(v);
+    return yes;
+}
+
+// The current stream of the current device (torch has been initialised there: it has made X).
+bool current_stream(void** out) {
+    PyObject* dev = PyObject_CallNoArgs(f_device);
+    if (!dev) return false;
+    PyObject* h = PyObject_CallOneArg(f_stream, dev);
+    Py_DECREF(dev);
+    if (!h) return false;
+    *out = PyLong_AsVoidPtr(h);
+    Py_DECREF(h);
+    return !PyErr_Occurred();
+}
+
+bool number(PyObject* v, float* out) {
+    const double d = PyFloat_AsDouble(v);
+    *out = (float)d;
+    return !(d == -1.0 && PyErr_Occurred());
+}
+
+// product(function address, kind, X, g, W1, W2, Y, eps)
+PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 8) return PyErr_Format(PyExc_TypeError, "eight arguments");
+    void* fn = PyLong_AsVoidPtr(a[0]);
+    const long kind = PyLong_AsLong(a[1]);
+    if (PyErr_Occurred()) return nullptr;
+    PyObject *X = a[2], *W1 = a[4];
+    void *x, *g = nullptr, *w1, *w2 = nullptr, *y, *stream;
+    int64_t mk[2], kn[2];
+    int32_t dtype;
+    float eps = 0.f;
+    if (!address(X, false, &x) || !on_gpu(X) || !address(a[3], true, &g) || !address(W1, false, &w1) ||
+        !address(a[5], kind != kGated && kind != kSwiglu, &w2) || !address(a[6], false, &y) || !sizes(X, 2, false, mk) ||
+        !sizes(W1, 2, true, kn) || !storage_type(X, &dtype) || !number(a[7], &eps) || !current_stream(&stream))
+        return not_mine();
+    int32_t st;
+    Py_BEGIN_ALLOW_THREADS
+    switch (kind) {
+        case kProduct: st = ((ProductFn)fn)(x, g, w1, y, mk[0], mk[1], kn[1], eps, dtype, stream); break;
+        case kGated: st = ((GatedFn)fn)(x, g, w1, w2, y, mk[0], mk[1], kn[1], eps, dtype, stream); break;
+        case kSwiglu: st = ((SwigluFn)fn)(x, w1, w2, y, mk[0], mk[1], kn[1], dtype, stream); break;
+        default: st = ((SoftmaxFn)fn)(x, w1, y, mk[0], mk[1], kn[1], dtype, stream); break;
+    }
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(st);
+}
+
+// attention(function address, Q, K, V, O, scale, qk_norm, eps)
+PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 8) return PyErr_Format(PyExc_TypeError, "eight arguments");
+    void* fn = PyLong_AsVoidPtr(a[0]);
+    if (PyErr_Occurred()) return nullptr;
+    void *q, *k, *v, *o, *stream;
+    int64_t bgd[3], bh[2];
+    int32_t dtype;
+    float scale, eps;
+    const int norm = PyObject_IsTrue(a[6]);
+    if (norm < 0 || !address(a[1], false, &q) || !on_gpu(a[1]) || !address(a[2], false, &k) || !address(a[3], false, &v) ||
+        !address(a[4], false, &o) || !sizes(a[1], 3, false, bgd) || !sizes(a[2], 2, true, bh) || !storage_type(a[1], &dtype) ||
+        !number(a[5], &scale) || !number(a[7], &eps) || !current_stream(&stream))
+        return not_mine();
+    int32_t st;
+    Py_BEGIN_ALLOW_THREADS
+    st = ((AttentionFn)fn)(q, k, v, o, bgd[0], bgd[1], bh[1], bgd[2], scale, norm, eps, dtype, stream);
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(st);
+}
+
+// setup(torch.Tensor, torch.nn.Parameter, float32, bfloat16, float16, current device, raw current stream of a device)
+PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    PyObject** to[] = {&t_tensor, &t_parameter, &dt_f32, &dt_bf16, &dt_f16, &f_device, &f_stream};
+    if (n != 7) return PyErr_Format(PyExc_TypeError, "seven arguments");
+    for (int i = 0; i < 7; ++i) {
+        Py_INCREF(a[i]);
+        Py_XSETREF(*to[i], a[i]);
+    }
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {{"product", (PyCFunction)(void (*)(void))product, METH_FASTCALL, nullptr},
+                         {"attention", (PyCFunction)(void (*)(void))attention, METH_FASTCALL, nullptr},
+                         {"setup", (PyCFunction)(void (*)(void))setup, METH_FASTCALL, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__marshal(void) {
+    s_shape = PyUnicode_InternFromString("shape");
+    s_dtype = PyUnicode_InternFromString("dtype");
+    s_is_cuda = PyUnicode_InternFromString("is_cuda");
+    s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
+    s_data_ptr = PyUnicode_InternFromString("data_ptr");
+    return PyModule_Create(&module);
+}

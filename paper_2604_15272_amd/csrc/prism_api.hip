@@ -265,6 +265,13 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     const bool ok64 = r64.S == 1 || n_tiles * ((M + 63) / 64) <= kMaxTickets;
     const double t32 = ok32 ? r32.us : 1e300, t64 = ok64 ? r64.us : 1e300;
     if (pf <= t32 && pf <= t64) return 0;
+    // Estimates within 6 %: the one whose partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64 rows
+    // need 8.5 MB, four of 32 rows half of that).
+    auto scratch = [&](const RowsEstimate& r) {
+        return r.S > 1 ? PRISM_WORKSPACE_HEADER_BYTES + (double)r.S * (gated ? 2 : 1) * (double)M * (double)N * 4.0 : 0.0;
+    };
+    if (t32 <= 1.06 * t64 && scratch(r64) > PRISM_STATIC_SCRATCH_BYTES - 65536.0 && scratch(r32) <= PRISM_STATIC_SCRATCH_BYTES - 65536.0)
+        return 2;
     return t32 <= t64 ? 2 : 4;
 }
 

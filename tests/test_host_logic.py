@@ -621,3 +621,13 @@ def test_inputs_are_deterministic_and_bf16_exact():
     f = pi.draw(pi.F32, 4, 64, 32, False, 5)
     assert np.array_equal(h["W"], f["W"].astype(np.float16))
     assert len(pi.WORKLOADS) == 5 and pi.WORKLOADS[1].N == 4096 and pi.WORKLOADS[3].gated
+
+
+def test_mid_size_calls_that_fit_the_static_scratch_by_either_row_count(P):
+    """32 and 64 rows per workgroup estimated nearly alike: the plan is the one whose partial sums fit."""
+    P.prism_diag_set_cu_count(256)
+    try:
+        for M, K, N in ((64, 8192, 4096), (62, 3000, 8192), (64, 11008, 4096)):
+            assert 0 < P.prism_workspace_bytes(P.PRISM_OP_RMSNORM_MATMUL, M, K, N, P.PRISM_BF16) <= P.STATIC_SCRATCH_BYTES
+    finally:
+        P.prism_diag_set_cu_count(0)

@@ -140,7 +140,8 @@ prism_status_t prism_softmax_matmul(const void* X, const void* W, void* Y, int64
  * no 1/sqrt(D): scale = 1 is the paper's operator.  The softmax over the keys is never written to
  * memory.  When the keys are split over workgroups (prism_attention_workspace_bytes > 0) the call
  * needs the registered workspace, under the same rules as the split-K calls above.
- * prism_attention_plan reports path, slices (split_k), keys per slice (tile_n), grid and workspace.
+ * prism_attention_plan reports path, slices (split_k), query heads per workgroup (tile_m), keys per slice
+ * (tile_n; 0: all keys), grid, threads and workspace.
  */
 prism_status_t prism_gqa_decode_attention(const void* Q, const void* K, const void* V, void* O,
                                           int64_t B, int64_t G, int64_t H, int64_t D, float scale,

@@ -20,7 +20,7 @@ namespace prism {
 
 namespace {
 
-constexpr int GW = 8;  // wavefronts per workgroup
+constexpr int GW = kGqaGeneralWaves;
 
 }  // namespace
 
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
 template <typename S, int D>
 static hipError_t launch_gqa_general_as(const AttentionCall& c) {
     typedef typename S::elem E;
-    dim3 grid((c.G + 15) / 16, c.B), block(GW * 64);
+    dim3 grid((c.G + kGqaGeneralHeads - 1) / kGqaGeneralHeads, c.B), block(GW * 64);
     constexpr size_t lds = (size_t)GW * 16 * (D + 2) * sizeof(float);
     auto kern = gqa_general_kernel<S, D>;
     static std::atomic<uint64_t> opted{0};

@@ -41,7 +41,7 @@ namespace prism {
 namespace {
 
 constexpr int AD = kAttnHeadDim;  // 128
-constexpr int ANW = 4;            // wavefronts per workgroup
+constexpr int ANW = kAttnThreads / 64;  // wavefronts per workgroup
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <typename T> __device__ __forceinline__ float at_ld(const T* p, size_t i);
@@ -337,7 +337,7 @@ hipError_t launch_gqa_16bit(const AttentionCall& c, bool f16, const AttentionPla
 }
 
 // ---- plain kernel -----------------------------------------------------------------------------------
-constexpr int kAtThreads = 256;
+constexpr int kAtThreads = kAttnThreads;
 constexpr int kAtColsPerThread = 4;  // head dimension up to 1024
 
 template <typename T>
@@ -432,7 +432,6 @@ static hipError_t launch_gqa_simple_t(const AttentionCall& c) {
 }
 
 hipError_t launch_gqa_simple(const AttentionCall& c, int dtype) {
-    if (c.D == 64 || c.D == 128) return launch_gqa_general(c, dtype);
     if (dtype == PRISM_F32) return launch_gqa_simple_t<float>(c);
     if (dtype == PRISM_F16) return launch_gqa_simple_t<_Float16>(c);
     return launch_gqa_simple_t<uint16_t>(c);

@@ -750,11 +750,13 @@ prism_status_t make_plan(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_d
 }
 
 // Attention: the matrix-core kernel for 16-bit storage, head dimension 128 and at most 16 query heads per
-// batch entry; the plain kernel otherwise (head dimension up to 1024).
+// batch entry; otherwise the fp32 matrix-core kernel for head dimensions 64 and 128 and the plain kernel for the others
+// up to 1024.
 prism_status_t make_attention_plan(int64_t B, int64_t G, int64_t H, int64_t D, prism_dtype_t dtype, AttentionPlan* p) {
     if (!dtype_known(dtype)) return PRISM_ERR_UNSUPPORTED;
     if (B < 0 || G < 0 || H <= 0 || D <= 0) return PRISM_ERR_INVALID_ARG;
-    *p = AttentionPlan{PRISM_PATH_SIMPLE, 1, 0, 0};
+    const AttentionPlan simple{PRISM_PATH_SIMPLE, 1, 0, 0, D == 64 || D == 128};
+    *p = simple;
     if (B == 0 || G == 0) return PRISM_OK;
     if (B > 65535 || G > 65535 || D > 1024 || H > 0x7FFFFFFF / 2048) return PRISM_ERR_UNSUPPORTED;
     const int forced = g_override.path.load();
@@ -786,9 +788,9 @@ prism_status_t make_attention_plan(int64_t B, int64_t G, int64_t H, int64_t D, p
     keys = ((H + S - 1) / S + 31) / 32 * 32;
     S = (H + keys - 1) / keys;  // no empty slice
     if (S > 1 && (uint64_t)B * S * 16 * kAttnHeadDim * 4 >= kTwoGiB) {
-        // 31-bit offsets into the partials: a batch this large is left to the plain kernel
+        // 31-bit offsets into the partials: a batch this large is left to the fp32 kernel
         if (forced == PRISM_PATH_ATTENTION) return PRISM_ERR_UNSUPPORTED;
-        *p = AttentionPlan{PRISM_PATH_SIMPLE, 1, 0, 0};
+        *p = simple;
         return PRISM_OK;
     }
     p->splits = (int)S;
@@ -999,7 +1001,7 @@ prism_status_t prism_gqa_decode_attention(const void* Q, const void* K, const vo
         }
         err = launch_gqa_16bit(c, dtype == PRISM_F16, plan, ws);
     } else {
-        err = launch_gqa_simple(c, (int)dtype);
+        err = plan.general ? launch_gqa_general(c, (int)dtype) : launch_gqa_simple(c, (int)dtype);
     }
     return err == hipSuccess ? PRISM_OK : PRISM_ERR_HIP;
 }
@@ -1018,11 +1020,12 @@ prism_status_t prism_attention_plan(int64_t B, int64_t G, int64_t H, int64_t D, 
     std::memset(out, 0, sizeof(*out));
     out->path = plan.path;
     out->split_k = plan.splits;
-    out->tile_m = plan.path == PRISM_PATH_ATTENTION ? 16 : 1;
+    const bool fast = plan.path == PRISM_PATH_ATTENTION;
+    out->tile_m = fast ? 16 : (plan.general ? kGqaGeneralHeads : 1);
     out->tile_n = plan.slice_keys;
-    out->grid_x = plan.path == PRISM_PATH_ATTENTION ? plan.splits : (int32_t)G;
+    out->grid_x = fast ? plan.splits : (int32_t)((G + out->tile_m - 1) / out->tile_m);
     out->grid_y = (int32_t)B;
-    out->block = 256;
+    out->block = !fast && plan.general ? 64 * kGqaGeneralWaves : kAttnThreads;
     out->workspace_bytes = plan.workspace_bytes;
     return PRISM_OK;
 }

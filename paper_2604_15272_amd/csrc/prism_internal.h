@@ -64,11 +64,17 @@ constexpr int kAttnMaxHeads = 16;
 constexpr int kAttnSliceKeys = 128;     // keys per workgroup for short contexts (one 32-key block per wavefront)
 constexpr int kAttnMaxSlices = 64;
 
+// The fp32 matrix-core attention kernel: query heads per workgroup, wavefronts.
+constexpr int kGqaGeneralHeads = 16;
+constexpr int kGqaGeneralWaves = 8;
+constexpr int kAttnThreads = 256;       // of the other two attention kernels
+
 struct AttentionPlan {
     int path;        // PRISM_PATH_SIMPLE or PRISM_PATH_ATTENTION
     int splits;      // key slices per batch entry
     int slice_keys;  // keys per slice (a multiple of 32)
     uint64_t workspace_bytes;
+    bool general;    // PRISM_PATH_SIMPLE: the fp32 matrix-core kernel, else the plain one
 };
 
 struct AttentionWorkspace {

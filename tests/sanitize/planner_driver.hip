@@ -26,6 +26,7 @@ hipError_t launch_probe_linear(const void*, unsigned long long, int, unsigned*, 
 hipError_t launch_softmax_simple(const SoftmaxCall&, int) { return hipSuccess; }
 hipError_t launch_gqa_16bit(const AttentionCall&, bool, const AttentionPlan&, const AttentionWorkspace&) { return hipSuccess; }
 hipError_t launch_gqa_simple(const AttentionCall&, int) { return hipSuccess; }
+hipError_t launch_gqa_general(const AttentionCall&, int) { return hipSuccess; }
 }  // namespace prism
 
 static uint64_t rng_state = 0x9E3779B97F4A7C15ull;

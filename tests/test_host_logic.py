@@ -208,6 +208,11 @@ def test_attention_arguments_and_plan(P):
     for shape in ((2, 8, 2048, 64), (2, 17, 2048, 128)):
         assert P.prism_attention_plan(*shape, f16)["path"] == P.PRISM_PATH_SIMPLE
     assert P.prism_attention_plan(2, 8, 2048, 128, P.PRISM_F32)["path"] == P.PRISM_PATH_SIMPLE
+    # of those, head dimensions 64 and 128: sixteen heads and eight wavefronts per workgroup; else a workgroup per head
+    for shape, dt, heads, grid_x, block in (((2, 8, 2048, 64), f16, 16, 1, 512), ((3, 17, 2048, 128), f16, 16, 2, 512),
+                                            ((2, 33, 2048, 128), P.PRISM_F32, 16, 3, 512), ((2, 7, 300, 80), f16, 1, 7, 256)):
+        p = P.prism_attention_plan(*shape, dt)
+        assert (p["tile_m"], p["grid_x"], p["grid_y"], p["block"]) == (heads, grid_x, shape[0], block), p
     P.prism_set_override(P.PRISM_PATH_ATTENTION, 0, 0)
     with pytest.raises(P.PrismError):
         P.prism_attention_plan(2, 8, 2048, 64, f16)

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(NTH, 4) void general_tiled_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
     const int q = lane >> 4, c = lane & 15;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * CW;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * CW;
     const bool gain = (flags & kFlagGain) != 0;
 
     // ---- staging maps: piece i of X is K values 4 xc .. of row xr + 64 i, piece i of W the columns 4 wc .. of row wr + 16 i
@@ -250,7 +250,7 @@ template <typename S, bool GATED, int BM>
 static hipError_t launch_general_tiled_as(const Call& c) {
     typedef typename S::elem E;
     constexpr int cw = GATED ? TC / 2 : TC;
-    dim3 grid((c.M + BM - 1) / BM, (c.N + cw - 1) / cw), block(NTH);
+    dim3 grid((c.N + cw - 1) / cw, (c.M + BM - 1) / BM), block(NTH);
     constexpr size_t lds = (size_t)2 * TK * (BM + TC) * 4 + BM * 4;
     auto kern = general_tiled_kernel<S, GATED, BM>;
     static std::atomic<uint64_t> opted{0};

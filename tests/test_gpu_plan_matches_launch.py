@@ -61,6 +61,26 @@ def _compare(plan, recorded):
     assert grid == (plan["grid_x"], plan["grid_y"], max(1, plan["grid_z"])) and block == (plan["block"], 1, 1), (plan, recorded)
 
 
+# fp32 and any shape: both kernels, narrow and wide, few rows and many; 16-bit: decode with and without K-slices, several row
+# groups, prefill; softmax: fp32, 16 rows, K-slices.
+@pytest.mark.parametrize("op,dtype,M,K,N", [
+    (0, "f32", 8, 256, 512), (0, "f32", 1000, 512, 3000), (1, "f32", 512, 1024, 4096), (0, "bf16", 8, 1023, 9001),
+    (1, "f16", 1021, 1201, 1023), (0, "f32", 3, 37, 3), (0, "bf16", 1999, 290, 2047), (0, "f16", 700, 13, 5001),
+    (0, "bf16", 16, 4096, 4096), (1, "bf16", 8, 4096, 14336), (1, "f16", 8, 1024, 4096), (0, "bf16", 8, 64, 64),
+    (0, "bf16", 200, 4096, 4096), (0, "bf16", 33, 520, 5128), (1, "bf16", 40, 512, 1024), (0, "bf16", 2048, 1024, 6144),
+    (1, "bf16", 1000, 512, 4096), (2, "f32", 100, 1000, 200), (2, "f16", 4096, 512, 128), (2, "f16", 16, 8192, 128),
+    (2, "bf16", 2000, 17, 900)])
+def test_products_and_softmax(P, op, dtype, M, K, N):
+    import torch
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    code = {"f32": P.PRISM_F32, "bf16": P.PRISM_BF16, "f16": P.PRISM_F16}[dtype]
+    X, W, Y = (torch.zeros(s, dtype=dt, device="cuda") for s in ((M, K), (K, N), (M, N)))
+    call = {0: lambda s: P.prism_rmsnorm_matmul(X, None, W, Y, stream=s),
+            1: lambda s: P.prism_rmsnorm_glu(X, None, W, W, Y, stream=s),
+            2: lambda s: P.prism_softmax_matmul(X, W, Y, stream=s)}[op]
+    _compare(P.prism_plan(op, M, K, N, code), _recorded(call))
+
+
 @pytest.mark.parametrize("dtype,B,G,H,D", [("f16", 2, 8, 2048, 128), ("bf16", 3, 5, 100, 128), ("f32", 2, 8, 2048, 128),
                                            ("f16", 2, 8, 2000, 64), ("bf16", 3, 33, 700, 128), ("f32", 3, 33, 20, 64),
                                            ("f32", 2, 7, 300, 80)])

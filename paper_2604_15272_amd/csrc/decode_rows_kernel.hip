@@ -40,7 +40,7 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
                                                          const uint16_t* __restrict__ W2, uint16_t* __restrict__ Y,
                                                          float* __restrict__ acc_part, float* __restrict__ ss_part,
                                                          unsigned* __restrict__ tickets, int M, int K, int N, float eps,
-                                                         int S, int flags) {
+                                                         int S, int flags, unsigned run) {
     constexpr int G = GATED ? 2 : 1;
     constexpr int RB = 16 * RG;  // rows per workgroup
     constexpr bool HALVES = GATED && RG == 4;  // wavefronts 0-3 take W1, 4-7 take W2
@@ -54,9 +54,10 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = lane >> 4, c = lane & 15;
-    // (order of the tiles: as in the 16-row kernel; 100 x 4096 x 8008 36.2 -> 30.5 us, 40 x 4096 x 5000 16.6 -> 15.2 us)
-    const int ntile = tiles_share_lines(N, gridDim.x) ? xcd_run_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x, split = blockIdx.y, rblock = blockIdx.z;
-    const int n_tiles = gridDim.x;
+    // (Nothing here asks for the grid's size: that is one more load before the first address of W is known.)
+    const int n_tiles = (N + TN - 1) / TN;
+    const int ntile = xcd_run_tile_of(blockIdx.x, run);
+    const int split = blockIdx.y, rblock = blockIdx.z;
     const int n0 = ntile * TN, m0 = rblock * RB;
 
     const int half = HALVES ? __builtin_amdgcn_readfirstlane(wave / LNW) : 0;
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
     }
 
     // With one row block W is read once and streamed past the caches; several row blocks share it through the L2.
-    const bool stream_w = gridDim.z == 1;
+    const bool stream_w = M <= RB;
     if constexpr (XLDS) {
         static_assert(!GATED, "calls with one weight matrix");
         // A load of X in MFMA operand layout (lane (q, c): row c, eight K values) touches sixteen rows for 64 bytes
@@ -419,7 +420,8 @@ static hipError_t launch_rows(const Call& c, int S, const DecodeWorkspace& ws) {
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, c.stream, (const uint16_t*)c.X, (const uint16_t*)c.g,
                        (const uint16_t*)c.W1, (const uint16_t*)(c.gated ? c.W2 : c.W1), (uint16_t*)c.Y, ws.acc_part,
-                       ws.ss_part, ws.tickets, c.M, c.K, c.N, c.eps, S, c.flags);
+                       ws.ss_part, ws.tickets, c.M, c.K, c.N, c.eps, S, c.flags,
+                       c.tile_runs ? (unsigned)n_tiles >> 3 : 0u);
     return hipGetLastError();
 }
 

@@ -137,14 +137,14 @@ __device__ __forceinline__ void wait_stores_acknowledged() { asm volatile("s_wai
 
 // Column tile of workgroup x of n, so that each of the eight XCDs (which take workgroups in turn) has a run of neighbouring
 // tiles.  Tiles whose rows do not start on a cache line share the lines at their edges, and only neighbours on the same XCD
-// find them in its L2.  (gridDim.x is a load of its own at the start of a kernel: 0.25 us of a decode call.)
-__device__ __forceinline__ int xcd_run_tile(unsigned x, unsigned n) {
-    const unsigned run = n >> 3;
-    return (int)(x < 8u * run ? (x & 7u) * run + (x >> 3) : x);
+// find them in its L2.  (gridDim.x is a load of its own at the start of a kernel: 0.25 us of a decode call.  So the host says which calls take runs.)
+__device__ __forceinline__ int xcd_run_tile_of(unsigned x, unsigned run) {  // run = n / 8; 0: tiles in order
+    // (A select by mask: a branch here splits the loads of the kernel's arguments in two that wait for each other, 0.2 to
+    // 0.5 us a call.)
+    const unsigned in_run = 0u - (unsigned)(x < 8u * run);
+    return (int)(x ^ ((x ^ ((x & 7u) * run + (x >> 3))) & in_run));
 }
-
-// Whether 16-bit column tiles of a row-major matrix of n columns share lines, and are enough for runs of five.
-__device__ __forceinline__ bool tiles_share_lines(int n, unsigned tiles) { return (n & 63) != 0 && tiles >= 40u; }
+__device__ __forceinline__ int xcd_run_tile(unsigned x, unsigned n) { return xcd_run_tile_of(x, n >> 3); }
 
 __device__ __forceinline__ float silu_f32(float a) {
     // a / (1 + exp(-a)); exp(-a) -> inf for very negative a gives a * 0 = -0.

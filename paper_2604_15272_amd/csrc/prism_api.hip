@@ -821,6 +821,13 @@ StreamPartition slow_tiles_first(const void* W, const void* W2, int64_t N, int64
     return sp;
 }
 
+// Whether a 16-bit decode call takes its column tiles in runs of neighbours, one run per XCD: where they share cache lines
+// (rows of W that are no multiple of 128 bytes): 8 x 4096 x 32008 55.3 -> 44.8 us, gated 4 x 4096 x 8008 31.0 -> 27.0 us, 8
+// x 4096 x 5000 (40 tiles) 12.4 -> 11.5 us, 100 x 4096 x 8008 36.2 -> 30.5 us, 40 x 4096 x 5000 16.6 -> 15.2 us.  Where they
+// don't, the plain order is the faster one (16 x 4096 x 4096 8.5 us, 9.4 us in runs), and with few tiles there are no runs
+// to speak of (gated 16 x 2048 x 4104, 33 tiles: 14.0 us, 14.5 us in runs).
+bool tiles_in_runs(int64_t N, int64_t n_tiles) { return (N & 63) != 0 && n_tiles >= 40; }
+
 // One call of the family: `flags` says which optional steps it takes (gain is dropped here when g
 // is null).
 prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, const void* W2, void* Y, int64_t M,
@@ -839,7 +846,7 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
     const prism_status_t st = make_plan(op, M, K, N, dtype, &plan);
     if (st != PRISM_OK) return st;
 
-    Call c{X, g, W1, gated ? W2 : nullptr, Y, (int)M, (int)K, (int)N, eps, gated, flags, stream, plan.general};
+    Call c{X, g, W1, gated ? W2 : nullptr, Y, (int)M, (int)K, (int)N, eps, gated, flags, stream, plan.general, false};
     hipError_t err = hipSuccess;
     switch (plan.pub.path) {
         case PRISM_PATH_SIMPLE:
@@ -885,15 +892,12 @@ prism_status_t run(prism_op_t op, const void* X, const void* g, const void* W1, 
                 }
             }
             if (plan.row_groups == 1 && sp.G == 0) sp = slow_tiles_first(W1, gated ? W2 : nullptr, N, plan.pub.grid_x, split, plan.packed);
-            // Neighbouring tiles on one XCD where they share cache lines (rows of W that are no multiple of 128 bytes): 8 x
-            // 4096 x 32008 55.3 -> 44.8 us, gated 4 x 4096 x 8008 31.0 -> 27.0 us, 8 x 4096 x 5000 (40 tiles) 12.4 -> 11.5 us.
-            // Where they don't, the plain order is the faster one (16 x 4096 x 4096 8.5 us, 9.4 us in runs), and with few
-            // tiles there are no runs to speak of (gated 16 x 2048 x 4104, 33 tiles: 14.0 us, 14.5 us in runs).
-            if (plan.row_groups == 1 && sp.G == 0 && (N & 63) != 0 && plan.pub.grid_x >= 40) {
+            if (plan.row_groups == 1 && sp.G == 0 && tiles_in_runs(N, plan.pub.grid_x)) {
                 sp = StreamPartition{};
                 sp.slow = 1;
                 sp.period = kTileRuns;
             }
+            c.tile_runs = plan.row_groups > 1 && tiles_in_runs(N, plan.pub.grid_x);
             err = plan.row_groups > 1
                       ? launch_decode_rows_16bit(c, dtype == PRISM_F16, plan.pub.split_k, plan.row_groups, plan.xlds, ws)
                       : launch_decode_16bit(c, dtype == PRISM_F16, split, sp, plan.waves, plan.packed, ws);

@@ -30,6 +30,7 @@ struct Call {
     int flags;  // kFlag* bits
     hipStream_t stream;
     GeneralForm form;  // of the fp32 kernel, where the call takes that path
+    bool tile_runs;    // multi-row decode kernel: column tiles in runs of neighbours, one run per XCD
 };
 
 // Members of the operator family (paper Section 7.1): which of the optional steps a call takes.

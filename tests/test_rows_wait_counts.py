@@ -6,6 +6,8 @@ import os
 import re
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2604_15272_amd")
 
@@ -42,17 +44,27 @@ def test_checker_sees_a_request_that_is_too_young():
     assert loads_after_requests("\n".join(asm)) == {k: (2, 2, 1)}
 
 
-def test_the_counted_wait_covers_every_request_of_x(tmp_path):
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
     spec = importlib.util.spec_from_file_location("_prism_build_for_test", os.path.join(PKG, "build.py"))
     b = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(b)
-    out = str(tmp_path / "rows.s")
+    out = str(tmp_path_factory.mktemp("asm") / "rows.s")
     cmd = [b.hipcc_path()] + [f for f in b.HIPCC_FLAGS if f not in ("-shared", "-fPIC")] + [
         "-S", "--cuda-device-only", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
         os.path.join(PKG, "csrc", "decode_rows_kernel.hip"), "-o", out]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
-    found = loads_after_requests(open(out).read())
+    return open(out).read()
+
+
+def test_the_counted_wait_covers_every_request_of_x(assembly):
+    found = loads_after_requests(assembly)
     assert len(found) == 8, sorted(found)  # 32 and 64 rows, one and several row blocks, two storage formats
     for name, (n, before, around) in found.items():
         assert n == 9 and before >= n and around >= n, (name, n, before, around)
+
+
+def test_the_kernel_does_not_ask_for_the_grid(assembly):
+    """The grid's size is a load that the first addresses of W would wait for; the host passes what depends on it."""
+    assert "decode_rows_kernel" in assembly and "hidden_block_count" not in assembly

@@ -176,22 +176,34 @@ void choose_prefill_tile(bool gated, int64_t M, int64_t N, int variant, int* bm,
 // More than 16 rows: which kernel family takes the call.  Returns the 16-row groups per workgroup of the decode
 // path's multi-row kernel (2 or 4: 32 or 64 rows), or 0 if the tiled prefill kernel is the better choice.
 //
-// The choice is made by a small time model of the three candidates, whose constants were measured on MI355X
-// (bf16, 96 shapes: 40 to 512 rows against K x N from 2048 x 8192 to 14336 x 4096, plain and gated, each forced
-// onto 32 rows, 64 rows and the prefill kernel): the model's pick is within 1.1 % of the best of the three on
-// average and within 10 % on every shape (the fixed rules it replaces: 4.3 % and 72 %).  Checked again on a second
-// grid (17 to 512 rows against ten K x N from 1024 x 4096 to 8192 x 28672, plain and gated, 300 calls), which the
-// HBM terms and the second-round factor come from: 0.2 % on average, 16 % at worst (2.4 % / 40 % for gated calls
-// before them).
-//   multi-row kernel, RG row groups, S K-slices, z row blocks, all times in microseconds:
-//     loop      = ceil(kblocks / S) x c x rounds (x 1.3 from the second round on, x 1.1 for two matrices),  c = 0.13 /
-//                 0.19 per K-block for 32 / 64 rows of one matrix, 0.33 / 0.60 for two (there a K-block's MFMAs, vector work
-//                 and 8 to 12 KiB through the L1 do not overlap); rounds = ceil(workgroups / compute units);
-//                 never less than streaming W at 5 / 6 TB/s (one / two matrices): once and 0.3 of that for every further
-//                 row block (one matrix), or once per row block when W is beyond 128 MB
-//   The constants of one matrix are of the pipelined loop (decode_rows_kernel.hip): 110 calls of 17 to 512 rows against
-//   eleven K x N from 512 x 3072 to 14336 x 4096, weights rotated through HBM: 0.9 % above the best of the candidates on
-//   average, 14 % at worst (8192 x 8192, 384 rows), none more than 1.7 % slower than with the constants before.
+// The choice is made by a small time model of the three candidates, whose constants were measured on MI355X.
+//
+// One weight matrix: 3000 calls of 17 to 512 rows against K x N from 64 x 64 to 14336 x 36000 (at most 1.2e8 weights, rotated
+// through HBM), every candidate forced: the choice is 0.95 % above the best on average (11 % on the worst hundredth), and
+// 1.1 % (17 %) on 1200 other calls; of those, 0.3 % are more than 2 % slower than the choice by the constants that were here
+// first (a regret of 2.2 %), the worst 11 %.  (Constants fitted to 110 calls with K from 512 on, in between, left out what a
+// round of workgroups costs: 237 x 64 x 16064 7.2 -> 17.5 us, 398 x 704 x 4672 13.6 -> 20.2 us, one call in ten 5 % or more.)
+//   multi-row kernel, S K-slices, z row blocks, microseconds:
+//     loop  = (1 + 1.3 x further rounds of workgroups) x (start + reduction 5.0 / 6.4 (32 / 64 rows) + 0.02 / 0.24 per
+//             K-block of a slice; X through LDS: 1.3 / 7.0 + 0.19 / 0.23 per K-block, in trips of sixteen)
+//     HBM   = W at 6.5 TB/s, and for every further row block a part of that again: 1.0 / 0.25 of it in several rounds, 0.64
+//             / 1.0 in one, half where all row blocks of a tile run on the same XCD (column tiles x slices a multiple of
+//             eight); + the start
+//     L2    = W once per row block and X once per column tile at 15 TB/s; + the start
+//     the longest of the three, and with S > 1 the exchange, 2.0 + 0.13 x S x row groups
+//   prefill kernel: (start + K steps x the step of the tile) x the rounds (x 0.5 for 128-row and smaller tiles, two of
+//     which share a compute unit), never less than W at 7 TB/s; + 2.1 for a full chip.
+//   At most four K-blocks in one round of workgroups: 32 rows (the two are close: 30 x 64 x 128 4.2 / 4.2 us, 106 x 128 x 1600 5.4 /
+//   5.2 us, 86 x 64 x 3328 4.7 / 5.1 us).
+//
+// Two weight matrices, or one of more than 128 MB (bf16, 96 shapes of 40 to 512 rows against K x N from 2048 x 8192 to 14336 x
+// 4096, then 17 to 512 rows against ten K x N from 1024 x 4096 to 8192 x 28672: 0.2 % on average, 16 % at worst):
+//   multi-row kernel, RG row groups, S K-slices, z row blocks:
+//     loop      = ceil(kblocks / S) x c x rounds (x 1.1 from the second round on),  c = 0.22 / 0.31 per K-block for 32 /
+//                 64 rows of one matrix, 0.33 / 0.60 for two (a K-block's MFMAs, vector work and 8 to 12 KiB through the L1
+//                 do not overlap); rounds = ceil(workgroups / compute units);
+//                 never less than streaming W at 6 TB/s: once, or once per row block when W is beyond 128 MB (48 rows as 2 x
+//                 32 against 4096 x 14336: 58.7 us, 47.3 us for 32 rows; 8192 x 28672: 321 against 156 us)
 //     reduction = 0.5 x RG x matrices (LDS)
 //     exchange  = 2.5 + S x RG x matrices / 8 when S > 1 (three dependent round trips, then the last arrival
 //                 pulls S partial tiles through one compute unit)
@@ -204,49 +216,86 @@ struct RowsEstimate {
     int64_t S;
 };
 
+// One weight matrix that the last-level cache (256 MB) keeps between the row blocks of a tile.
+bool rows_model_fits(bool gated, int64_t K, int64_t N) { return !gated && (uint64_t)K * N * 2 <= 128000000ull; }
+
+// K-slices of the multi-row kernel: what fills the compute units, in slices of at least eight K-blocks; a little over one
+// round (260 tiles: 101.1 -> 99.8 us plain with 64 rows, 161.3 -> 148.3 us gated with 32 rows; 320 tiles are better left
+// unsplit: 93.7 against 95.1 us) two.
+int64_t rows_slices(int64_t wgs, int64_t kblocks, int64_t cus) {
+    int64_t S = wgs <= cus ? cus / wgs : 1;
+    if (S <= 1 && wgs > cus && wgs * 10 < cus * 12 && kblocks >= 32) S = 2;
+    return std::max<int64_t>(1, std::min<int64_t>(S, kblocks / 8));
+}
+
+// One weight matrix: X through LDS or straight into operand registers, by the K-blocks of a slice (4200 calls, both forms
+// forced; times of LDS against straight).  32 rows: a trip of the eight wavefronts is sixteen K-blocks either way, and the
+// straight form has all of them in flight at once, but fetches X in narrow pieces: 1 to 2 K-blocks +13 %, 3 to 4 +4 %, 5 to 8 -5
+// %, 9 to 12 -2 %, 13 to 16 +2 %, 17 to 20 0 %, 21 to 24 -4 %, 25 to 48 -1 %, then -2 to -7 %.  64 rows: up to 31 K-blocks +4 to
+// +16 %, 32 to 48 +2 to +4 %, 49 to 56 0 to +1 %, 57 to 64 +1 to -8 %, then -2 to -12 %.
+bool rows_x_through_lds(int row_groups, int64_t slice_blocks) {
+    if (row_groups == 2) return slice_blocks >= 21 || (slice_blocks >= 5 && slice_blocks <= 12);
+    return slice_blocks >= 57;
+}
+
 RowsEstimate rows_estimate(int rg, bool gated, int64_t M, int64_t K, int64_t N, int64_t cus) {
-    const int G = gated ? 2 : 1;
     const int64_t n_tiles = (N + kDecodeTileN - 1) / kDecodeTileN, kblocks = (K + kDecodeKBlock - 1) / kDecodeKBlock;
     const int64_t z = (M + 16 * rg - 1) / (16 * rg), wgs1 = n_tiles * z;
+    const double w_bytes = 2.0 * (double)K * (double)N;
+    if (rows_model_fits(gated, K, N)) {
+        struct C {
+            double start, per_k, start_lds, per_k_lds, again_rounds, again_xcd, again;
+        };
+        static const C consts[2] = {{5.0, 0.02, 1.3, 0.19, 1.0, 0.52, 0.64}, {6.4, 0.24, 7.0, 0.23, 0.25, 0.53, 1.0}};
+        const C& k = consts[rg / 2 - 1];
+        const int64_t S = rows_slices(wgs1, kblocks, cus), slice = (kblocks + S - 1) / S, rounds = (wgs1 * S + cus - 1) / cus;
+        const double loop = rows_x_through_lds(rg, slice) ? k.start_lds + k.per_k_lds * (double)((slice + 15) / 16 * 16)
+                                                          : k.start + k.per_k * (double)slice;
+        const double again = rounds > 1 ? k.again_rounds : ((n_tiles * S) % 8 == 0 ? k.again_xcd : k.again);
+        const double hbm = w_bytes / 6.5e6 * (1.0 + again * (double)(z - 1));
+        const double l2 = (w_bytes * (double)z + 2.0 * (double)M * (double)K * (double)n_tiles) / 15.0e6;
+        const double us = std::max(loop * (1.0 + 1.3 * (double)(rounds - 1)), std::max(hbm, l2) + k.start);
+        return RowsEstimate{S > 1 ? us + 2.0 + 0.13 * (double)(S * rg) : us, S};
+    }
+    const double G = gated ? 2.0 : 1.0;
     int64_t S = wgs1 <= cus ? cus / wgs1 : 1;
     S = std::max<int64_t>(1, std::min<int64_t>(S, std::max<int64_t>(1, kblocks / 8)));
-    const double c = gated ? (rg == 2 ? 0.33 : 0.60) : (rg == 2 ? 0.13 : 0.19);
+    const double c = gated ? (rg == 2 ? 0.33 : 0.60) : (rg == 2 ? 0.22 : 0.31);
     const int64_t rounds = (wgs1 * S + cus - 1) / cus;
-    double loop = (double)((kblocks + S - 1) / S) * c * (double)rounds * (rounds >= 2 ? (gated ? 1.1 : 1.3) : 1.0);
+    double loop = (double)((kblocks + S - 1) / S) * c * (double)rounds * (rounds >= 2 ? 1.1 : 1.0);
     // Never faster than W streams from HBM; weights too large for the last-level cache to keep between the row
-    // blocks of a tile (256 MB; 128 MB taken) stream once per row block (gated 4096 x 14336, 48 rows as 2 x 32:
-    // 58.7 us against 47.3 us for 32 rows; 8192 x 28672: 321 against 156 us), smaller ones still cost a part of that (one
-    // matrix, 4096 x 14336, 48 rows: 32.2 us as 2 x 32, 28.2 us as 1 x 64).
-    const double w_bytes = 2.0 * (double)K * (double)N * G;
-    const double reads = w_bytes > 128.0e6 ? (double)z : (gated ? 1.0 : 1.0 + 0.3 * (double)(z - 1));
-    loop = std::max(loop, w_bytes / (gated ? 6.0e6 : 5.0e6) * reads);
+    // blocks of a tile (256 MB; 128 MB taken) stream once per row block.
+    loop = std::max(loop, G * w_bytes / 6.0e6 * (G * w_bytes > 128.0e6 ? (double)z : 1.0));
     double us = loop + 0.5 * rg * G + 1.5;
-    if (S > 1) us += 2.5 + (double)(S * rg * G) / 8.0;
+    if (S > 1) us += 2.5 + (double)(S * rg) * G / 8.0;
     return RowsEstimate{us, S};
 }
 
 double prefill_estimate(bool gated, int64_t M, int64_t K, int64_t N, int64_t cus) {
     struct T {
         int bm, bn;
-        double step;
+        double step, fit_start, fit_step;  // the latter two of the first model
     };
-    static const T plain[] = {{256, 256, 1.5}, {256, 192, 1.5}, {256, 128, 1.25}, {128, 128, 0.88}, {64, 64, 0.93}};
+    static const T plain[] = {{256, 256, 1.5, 9.8, 1.6}, {256, 192, 1.5, 8.3, 1.3}, {256, 128, 1.25, 6.1, 1.0},
+                              {128, 128, 0.88, 4.0, 0.73}, {64, 64, 0.93, 3.5, 0.68}};
     static const T gate[] = {{256, 256, 2.0}, {128, 256, 1.2}, {128, 128, 0.90}};
     // The tile the call would get (choose_prefill_tile), not the best of all: the estimate is of what would run.
     int bm = 0, bn = 0;
     choose_prefill_tile(gated, M, N, 0, &bm, &bn);
-    double step = 1.5;
-    for (const T& t : plain)
-        if (!gated && t.bm == bm && t.bn == bn) step = t.step;
-    for (const T& t : gate)
-        if (gated && t.bm == bm && t.bn == bn) step = t.step;
+    const T* t = gated ? gate : plain;
+    while (t->bm != bm || t->bn != bn) ++t;
     const int64_t KT = (K + 63) / 64;
     const int64_t cw = gated ? bn / 2 : bn;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + cw - 1) / cw);
     const bool shares_cu = bm <= 128 && bn <= 128;
-    const double f = tiles <= cus ? 1.0 : ((shares_cu && tiles <= 2 * cus) ? 1.2 : (double)((tiles + cus - 1) / cus));
+    const double w_bytes = 2.0 * (double)K * (double)N * (gated ? 2 : 1), fill = (double)tiles / (double)cus;
+    if (rows_model_fits(gated, K, N)) {
+        const double f = tiles <= cus ? 1.0 : (shares_cu ? 1.0 + 0.5 * (fill - 1.0) : std::ceil(fill));
+        return std::max((t->fit_start + (double)KT * t->fit_step) * f, w_bytes / 7.0e6 + t->fit_start) + 2.1 * std::min(1.0, fill);
+    }
+    const double f = tiles <= cus ? 1.0 : ((shares_cu && tiles <= 2 * cus) ? 1.2 : std::ceil(fill));
     // (the tiled kernel streams W from HBM at about 5 TB/s at best: gated 17 x 8192 x 28672 193 us)
-    return std::max((double)KT * step * f, 2.0 * (double)K * (double)N * (gated ? 2 : 1) / 5.0e6) + 3.0;
+    return std::max((double)KT * t->step * f, w_bytes / 5.0e6) + 3.0;
 }
 
 int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
@@ -259,19 +308,20 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     if (gated && K <= 64 && z32 <= 65535 && n_tiles * z32 <= kMaxTickets) return 2;
     if (M > kDecodeRowsMax) return 0;
     const RowsEstimate r32 = rows_estimate(2, gated, M, K, N, cus), r64 = rows_estimate(4, gated, M, K, N, cus);
-    const double pf = prefill_estimate(gated, M, K, N, cus);
+    // (weights past the prefill kernel's 31-bit offsets would end up on the fp32 kernel)
+    const double pf = (uint64_t)K * N * 2 >= kTwoGiB ? 1e300 : prefill_estimate(gated, M, K, N, cus);
     // the arrival counters of a split call: one per (column tile, row block)
     const bool ok32 = r32.S == 1 || n_tiles * z32 <= kMaxTickets;
     const bool ok64 = r64.S == 1 || n_tiles * ((M + 63) / 64) <= kMaxTickets;
     const double t32 = ok32 ? r32.us : 1e300, t64 = ok64 ? r64.us : 1e300;
+    if (rows_model_fits(gated, K, N) && ok32 && K <= 4 * kDecodeKBlock && n_tiles * z32 <= cus) return 2;
     if (pf <= t32 && pf <= t64) return 0;
-    // Estimates within 6 %: the one whose partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64 rows
-    // need 8.5 MB, four of 32 rows half of that).
-    auto scratch = [&](const RowsEstimate& r) {
-        return r.S > 1 ? PRISM_WORKSPACE_HEADER_BYTES + (double)r.S * (gated ? 2 : 1) * (double)M * (double)N * 4.0 : 0.0;
+    // Estimates within 11 %: 32 rows where only their partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64
+    // rows need 8.5 MB, four of 32 rows half of that; 22.6 / 23.2 us).
+    auto fits_scratch = [&](const RowsEstimate& r) {
+        return r.S == 1 || PRISM_WORKSPACE_HEADER_BYTES + (double)r.S * (gated ? 2 : 1) * (double)M * (double)N * 4.0 <= PRISM_STATIC_SCRATCH_BYTES - 65536.0;
     };
-    if (t32 <= 1.06 * t64 && scratch(r64) > PRISM_STATIC_SCRATCH_BYTES - 65536.0 && scratch(r32) <= PRISM_STATIC_SCRATCH_BYTES - 65536.0)
-        return 2;
+    if (t32 <= 1.11 * t64 && fits_scratch(r32) && !fits_scratch(r64)) return 2;
     return t32 <= t64 ? 2 : 4;
 }
 
@@ -589,7 +639,7 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
             // The 16-row kernel: the nearest number of slices, but never a grid that needs a second round for a few
             // workgroups (X[16,4096] . W[4096,11008], 86 tiles: 20.8 us with 2 slices, 27.7 us with 3; W[4096,7168],
             // 56 tiles: 14.9 us with 4, 20.3 us with 5).
-            S = (row_groups > 1) ? target / wgs : (target + wgs / 2) / wgs;
+            S = (row_groups > 1) ? rows_slices(wgs, kblocks, target) : (target + wgs / 2) / wgs;
             if (row_groups == 1 && wgs * S > target && wgs <= target) S = target / wgs;
             // 129 to 159 tiles: one slice per tile leaves more than a third of the CUs idle and two make a second
             // round of a few workgroups; three (1.5 to 1.9 rounds of shorter workgroups, dealt out as CUs free up)
@@ -602,9 +652,6 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
             // with 4 slices; W[4096,40960], 320 tiles, 72.2 / 65.1 us; W[4096,49152], 384 tiles, 76.0 us, 73.7 us
             // with 2 slices; but W[4096,51200], 400 tiles, 76.3 us unsplit against 81.5 us with 3, and from 512
             // tiles on (520, 640 tiles measured) slices change nothing or cost time.
-            // The multi-row kernel, a little over one round (260 tiles: 101.1 -> 99.8 us plain with 64 rows, 161.3 ->
-            // 148.3 us gated with 32 rows; 320 tiles are better left unsplit: 93.7 against 95.1 us).
-            if (row_groups > 1 && S <= 1 && wgs > target && wgs * 10 < target * 12 && kblocks >= 32) S = 2;
             if (row_groups == 1 && S == 1 && wgs > target && wgs < 2 * target) {
                 auto fill = [&](int64_t s) { return (double)(wgs * s) / (double)(target * ((wgs * s + target - 1) / target)); };
                 if (fill(1) < 0.77) {
@@ -691,15 +738,8 @@ prism_status_t make_plan_with(prism_op_t op, int64_t M, int64_t K, int64_t N, pr
                 }
             }
         }
-        // X through LDS or straight loads (one matrix; us, LDS / straight).  32 rows per workgroup: LDS, except a single row
-        // block in slices of 9 to 31 K-blocks, where W streams and few wavefronts have a next block to fetch (128 x 4096 x
-        // 4096 15.4 / 17.2, 32 x 8192 x 8192 27.8 / 29.0, 32 x 1024 x 4096, eight K-blocks, 9.0 / 9.9; but 17 x 4096 x 4096,
-        // sixteen K-blocks, 13.0 / 12.1).  64 rows: LDS from 48 K-blocks a slice (512 x 4096 x 4096 28.1 / 32.2, 64 x 14336 x
-        // 4096 30.2 / 31.9; but 128 x 4096 x 4096, 32 K-blocks, 17.5 / 17.2, 48 x 4096 x 6144, 26 K-blocks, 20.1 / 18.6).
         const int64_t slice_blocks = (kblocks + S - 1) / std::max<int64_t>(1, S);
-        if (row_groups > 1 && !gated && variant == 0 &&
-            (row_groups == 2 ? (row_blocks > 1 || slice_blocks >= 32 || slice_blocks <= 8) : slice_blocks >= 48))
-            xlds = true;
+        if (row_groups > 1 && !gated && variant == 0 && rows_x_through_lds(row_groups, slice_blocks)) xlds = true;
         out->waves = waves;
         out->row_groups = row_groups;
         out->xlds = xlds;

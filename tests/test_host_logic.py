@@ -636,3 +636,27 @@ def test_mid_size_calls_that_fit_the_static_scratch_by_either_row_count(P):
             assert 0 < P.prism_workspace_bytes(P.PRISM_OP_RMSNORM_MATMUL, M, K, N, P.PRISM_BF16) <= P.STATIC_SCRATCH_BYTES
     finally:
         P.prism_diag_set_cu_count(0)
+
+
+def test_mid_size_calls_of_shallow_k_and_wide_n_take_the_faster_kernel(P):
+    """17 to 512 rows, one matrix: what a round of workgroups costs decides these, not the K-blocks.  Forms as timed on an
+    MI355X (us, as 32 rows / 64 rows / prefill kernel)."""
+    P.prism_diag_set_cu_count(256)
+    try:
+        rows = lambda M, K, N: (lambda p: (p["path"], p["tile_m"] if p["path"] == P.PRISM_PATH_DECODE else 0))(
+            P.prism_plan(P.PRISM_OP_RMSNORM_MATMUL, M, K, N, P.PRISM_BF16))
+        prefill, few, many = (P.PRISM_PATH_PREFILL, 0), (P.PRISM_PATH_DECODE, 32), (P.PRISM_PATH_DECODE, 64)
+        assert rows(237, 64, 16064) == prefill      # 15.1 / 13.3 / 7.1
+        assert rows(489, 128, 5760) == prefill      # 13.5 / 13.8 / 6.8
+        assert rows(392, 128, 9984) == prefill      # 17.5 / 18.9 / 9.0
+        assert rows(359, 704, 33664) == prefill     # 112.5 / 77.5 / 37.4
+        assert rows(88, 512, 20224) == prefill      # 16.2 / 18.2 / 12.1
+        assert rows(411, 4224, 8448) == prefill     # 138.1 / 83.2 / 70.1
+        assert rows(58, 320, 22912) != few          # 12.6 / 9.5 / 10.5
+        assert rows(54, 4592, 9064) == many         # 39.2 / 27.8 / 56.5
+        assert rows(30, 64, 128) == few             # 4.2 / 6.1 / 4.2
+        assert rows(128, 4096, 4096) == many        # 20.9 / 19.5 / 50.9
+        assert rows(64, 4096, 4096) == few          # 15.8 / 17.2 / 51.0
+        assert rows(512, 2048, 2048) == few         # 12.1 / 16.4 / 20.1
+    finally:
+        P.prism_diag_set_cu_count(0)

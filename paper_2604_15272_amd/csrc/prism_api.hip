@@ -370,12 +370,42 @@ Choice resolve_choice(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_dtyp
 // 1024 x 4096 94 us with four, 100 us with eight; fp32 1 x 4096 x 4096 29 us with four, 21 us with eight.
 // Softmax: eight, or sixteen of the narrowest tile where half the compute units get none (fp32 8 x 16384 x 64 62 us with eight,
 // 57 us with sixteen; products gain nothing).
+// Shallow K (at most 128): the fixed part of a workgroup counts, that is its wavefronts' start and the reduction across them,
+// and with many outputs their stores.  By the outputs, in units of 16 x 64 per compute unit (600 products and 420 softmax calls
+// of 1 to 30000 rows and columns, every form with 1, 2, 4 and 8 wavefronts forced; us, this rule / the estimate above):
+//   products: both operands through LDS from 8 units (128 rows) or 4 (64 rows) on, whose workgroup keeps its sums in registers
+//     (bf16 17797 x 3 x 5180 102 / 437, gated f16 23078 x 2 x 2875 175 / 605, bf16 gated 18501 x 24 x 725 46 / 138); else the
+//     narrowest tile with 2 wavefronts (4 beyond K = 64); below 0.4 units the estimate above is as good.
+//   softmax: one wavefront from 2 units on (64 columns from 8 on, and that up to K = 320), 2 from 1 on, else 4 (fp32 15281 x 2 x 499
+//     31 / 104, bf16 7197 x 22 x 1602 40 / 135, fp32 6844 x 16 x 394 16 / 44).
+// 3 to 4 % above the best form on average.  The kernels with one thread per column that were here before are still up to 20 %
+// faster for K < 8 with millions of outputs (gated bf16 2612 x 3 x 13370 82 / 100 us).
+bool shallow_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, GeneralForm* out) {
+    const double units = (double)((N + 63) / 64) * (double)((M + 15) / 16) / (double)cu_count();
+    if (K > (softmax && units >= 8.0 ? 320 : 128)) return false;
+    if (softmax) {
+        *out = GeneralForm{1, units >= 8.0 && N >= 4 ? 4 : 1, units >= 2.0 ? 1 : (units >= 1.0 ? 2 : 4)};
+        return true;
+    }
+    if (N >= 32 && units >= 4.0 && M >= 128 && (N + 63) / 64 <= 65535) {
+        *out = GeneralForm{units >= 8.0 ? 8 : 4, gated ? 4 : 8, 8};
+        return true;
+    }
+    if (units < 0.4) return false;
+    *out = GeneralForm{1, 1, K <= 64 ? 2 : 4};
+    return true;
+}
+
 GeneralForm choose_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype) {
     struct Form { int rg, vw; double w16; };
     static const Form forms[] = {{1, 8, 12.0}, {2, 4, 8.0}, {1, 4, 8.0}, {2, 1, 6.0}, {1, 1, 6.0}};
     const bool wide = dtype == PRISM_F32;
     const double cus = (double)cu_count(), G = gated ? 2.0 : 1.0;
     GeneralForm best{1, 1, 8};
+    if (shallow_general_form(gated, softmax, M, K, N, &best)) {
+        if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
+        return best;
+    }
     double best_t = 1e300;
     for (const Form& f : forms) {
         if (f.vw > N || (f.vw == 8 && wide) || (f.rg == 2 && M <= 16)) continue;

@@ -102,6 +102,26 @@ def test_softmax_any_shape_masked_and_non_finite(P, dtype):
                                atol=1e-5 if dtype == pi.F32 else 2.5e-3, equal_nan=True)
 
 
+# Shallow K: a few wavefronts on the narrowest tile, fewer K-blocks than wavefronts, or everything through LDS.
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
+@pytest.mark.parametrize("M,K,N,gated,form", [(300, 5, 515, False, (16, 16, 128)), (301, 33, 515, True, (16, 16, 128)),
+                                              (70, 101, 2050, False, (16, 16, 256)), (1999, 3, 2047, False, (128, 128, 512)),
+                                              (1999, 37, 1023, True, (64, 64, 512)), (3001, 17, 1001, True, (128, 64, 512))])
+def test_shallow_k_forms(P, dtype, M, K, N, gated, form):
+    plan = P.prism_plan(int(gated), M, K, N, DTYPE_CODE[dtype])
+    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
+    _case(P, dtype, M, K, N, gated, seed=290 + K, expect_path=P.PRISM_PATH_SIMPLE)
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
+@pytest.mark.parametrize("M,K,N,form", [(33, 125, 67, (16, 16, 256)), (1001, 3, 259, (16, 16, 128)), (2001, 45, 259, (16, 16, 64)),
+                                        (8001, 97, 259, (16, 64, 64)), (35001, 1, 3, (16, 16, 64))])
+def test_softmax_shallow_k_forms(P, dtype, M, K, N, form):
+    plan = P.prism_plan(P.PRISM_OP_SOFTMAX_MATMUL, M, K, N, DTYPE_CODE[dtype])
+    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
+    _softmax_case(P, dtype, M, K, N, seed=295 + K, expect_path=P.PRISM_PATH_SIMPLE)
+
+
 # The same with both operands in LDS (64 and 128 rows per workgroup): ragged rows and columns on either side of a tile, K
 # with a rest; then a whole number of stages, and less than one.
 @pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])

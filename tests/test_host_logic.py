@@ -660,3 +660,26 @@ def test_mid_size_calls_of_shallow_k_and_wide_n_take_the_faster_kernel(P):
         assert rows(512, 2048, 2048) == few         # 12.1 / 16.4 / 20.1
     finally:
         P.prism_diag_set_cu_count(0)
+
+
+def test_fp32_forms_of_shallow_k(P):
+    """(rows, columns, threads) per workgroup where K is shallow, with the times of an MI355X (us, this form / sixteen rows with
+    the wavefronts that a deep K takes)."""
+    P.prism_diag_set_cu_count(256)
+    try:
+        def form(op, dt, M, K, N):
+            p = P.prism_plan(op, M, K, N, dt)
+            assert p["path"] == P.PRISM_PATH_SIMPLE
+            return p["tile_m"], p["tile_n"], p["block"]
+        f32, bf16, f16 = P.PRISM_F32, P.PRISM_BF16, P.PRISM_F16
+        assert form(0, bf16, 17797, 3, 5180) == (128, 128, 512)   # 102 / 437
+        assert form(1, bf16, 18501, 24, 725) == (128, 64, 512)    # 46 / 138
+        assert form(0, bf16, 1120, 5, 1007) == (64, 128, 512)     # 6.8 / 15.8
+        assert form(0, f32, 21350, 94, 13)[1] != 128              # 13.2 in 128 columns, 5.9 in 16
+        assert form(0, f16, 38, 4, 19400) == (16, 16, 128)        # 6.9 / 10.9
+        assert form(2, f32, 15281, 2, 499) == (16, 64, 64)        # 31 / 104
+        assert form(2, f32, 6844, 16, 394) == (16, 64, 64)        # 15 / 44
+        assert form(2, f16, 382, 10, 3004) == (16, 16, 64)        # 9.9 / 20.3
+        assert form(2, f16, 1000, 36, 200) == (16, 16, 256)
+    finally:
+        P.prism_diag_set_cu_count(0)

@@ -24,7 +24,7 @@ constexpr int GW = kGqaGeneralWaves;
 
 }  // namespace
 
-// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums.
+// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums, [GW][16] weights, [16] denominators.
 template <typename S, int D>
 __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::elem* __restrict__ Q,
                                                               const typename S::elem* __restrict__ K,
@@ -43,6 +43,8 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
     float* red = lds;
     float* wave_max = lds + GW * 16 * D;
     float* wave_sum = wave_max + GW * 16;
+    float* weight = wave_sum + GW * 16;
+    float* total = weight + GW * 16;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,29 +169,52 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
 
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
+    // Across the wavefronts that had keys.  Their weights and the denominator once per head: while every output element worked
+    // them out for itself this part took a third of a call of few keys (f16 2 x 44 x 4 x 128 7.4 -> 5.5 us, fp32 32 x 16 x 64 x
+    // 128 9.1 -> 7.7 us), which made those slower than the plain kernel (5.0 us; in fp32 with at most 24 keys of 128 it still
+    // is by up to 15 %).
+    const int active = min(GW, (H + 15) / 16);
     if (q == 0) {
         wave_max[wave * 16 + c] = m_run;
         wave_sum[wave * 16 + c] = l_run;
     }
+    if (wave < active) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * D + VW * c + j] = acc[j][e];
+            for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * D + VW * c + j] = acc[j][e];
+    }
     __syncthreads();
-    for (int o = tid; o < 16 * D; o += GW * 64) {
-        const int head = o / D, col = o % D;
-        if (g0 + head >= G) break;  // (heads rise with o)
+    if (tid < 16 * GW) {
+        const int head = tid & 15, mine = tid >> 4;
         float gmax = -__builtin_inff();
-        for (int w = 0; w < GW; ++w) gmax = fmaxf(gmax, wave_max[w * 16 + head]);
-        float v = 0.f, den = 0.f;
-        for (int w = 0; w < GW; ++w) {
+        for (int w = 0; w < active; ++w) gmax = fmaxf(gmax, wave_max[w * 16 + head]);
+        float den = 0.f;
+        for (int w = 0; w < active; ++w) {
             const float mw = wave_max[w * 16 + head];
-            // A wavefront without keys, or with none above -inf, is relative to 0 and weighs nothing; a NaN in its sums stays one.
+            // A wavefront with no key above -inf is relative to 0 and weighs nothing; a NaN in its sums stays one.
             const float f = (mw == -__builtin_inff()) ? 0.f : expf(mw - gmax);
-            v = fmaf(f, red[(w * 16 + head) * D + col], v);
             den = fmaf(f, wave_sum[w * 16 + head], den);
+            if (w == mine) weight[w * 16 + head] = f;
         }
-        O[((size_t)bi * G + g0 + head) * D + col] = S::narrow(v / den);
+        if (mine == 0) total[head] = den;
+    }
+    __syncthreads();
+    // A thread's outputs together: one after the other they would wait for the LDS in turn.
+    constexpr int PER = 16 * D / (GW * 64);
+    float v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = 0.f;
+    for (int w = 0; w < active; ++w)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int o = tid + i * (GW * 64);
+            v[i] = fmaf(weight[w * 16 + o / D], red[w * 16 * D + o], v[i]);
+        }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int o = tid + i * (GW * 64), head = o / D;
+        if (g0 + head < G) O[((size_t)bi * G + g0) * D + o] = S::narrow(v[i] / total[head]);
     }
 }
 
@@ -197,7 +222,7 @@ template <typename S, int D>
 static hipError_t launch_gqa_general_as(const AttentionCall& c) {
     typedef typename S::elem E;
     dim3 grid((c.G + kGqaGeneralHeads - 1) / kGqaGeneralHeads, c.B), block(GW * 64);
-    constexpr size_t lds = (size_t)GW * 16 * (D + 2) * sizeof(float);
+    constexpr size_t lds = ((size_t)GW * 16 * (D + 3) + 16) * sizeof(float);
     auto kern = gqa_general_kernel<S, D>;
     static std::atomic<uint64_t> opted{0};
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;

@@ -850,6 +850,13 @@ def test_attention_fp32_matrix_core_kernel(P, dtype, D, B, G, H, qk_norm):
     _attention_case(P, dtype, B, G, H, D, seed=770 + H, scale=D ** -0.5, qk_norm=qk_norm, expect_path=P.PRISM_PATH_SIMPLE)
 
 
+# From one block of keys to one more than there are wavefronts: which of them take part in the combination.
+@pytest.mark.parametrize("dtype,D", [(pi.F32, 64), (pi.F32, 128), (pi.BF16, 64), (pi.F16, 64)])
+@pytest.mark.parametrize("B,G,H", [(2, 16, 17), (1, 17, 33), (3, 9, 112), (2, 16, 113), (2, 5, 129), (1, 40, 144)])
+def test_attention_fp32_kernel_with_few_blocks_of_keys(P, dtype, D, B, G, H):
+    _attention_case(P, dtype, B, G, H, D, seed=795 + H, scale=D ** -0.5, qk_norm=False, expect_path=P.PRISM_PATH_SIMPLE)
+
+
 @pytest.mark.parametrize("dtype", [pi.BF16, pi.F16])
 def test_attention_more_heads_than_the_16_bit_kernel_takes(P, dtype):
     _attention_case(P, dtype, 2, 40, 333, 128, seed=790, scale=128 ** -0.5, expect_path=P.PRISM_PATH_SIMPLE)

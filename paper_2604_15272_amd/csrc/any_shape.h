@@ -22,6 +22,11 @@ struct StoreF16 {
     static __device__ __forceinline__ elem narrow(float v) { return (elem)v; }
 };
 
+constexpr float kFloatMax = 3.402823466e38f;
+
+// NaN if x is one or an infinity, else t.
+__device__ __forceinline__ float not_finite(float x, float t) { return fmaf(x, 0.f, t); }
+
 // V consecutive elements, loaded in one piece from an address that is only aligned to one of them.
 template <typename E, int V> struct Piece {
     typedef E vec __attribute__((ext_vector_type(V)));

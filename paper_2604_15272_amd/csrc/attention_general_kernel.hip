@@ -24,7 +24,7 @@ constexpr int GW = kGqaGeneralWaves;
 
 }  // namespace
 
-// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums, [GW][16] weights, [16] denominators.
+// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums, [GW][16] weights, [16] denominators, [GW] flags.
 template <typename S, int D>
 __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::elem* __restrict__ Q,
                                                               const typename S::elem* __restrict__ K,
@@ -45,6 +45,7 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
     float* wave_sum = wave_max + GW * 16;
     float* weight = wave_sum + GW * 16;
     float* total = weight + GW * 16;
+    float* wave_bad = total + 16;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -146,45 +147,66 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
     };
     // Two named blocks in turn, without a condition between a load and its use (general_kernel.hip).
     const int nfull = H / 16;
-    if (wave < nfull) {
-        const int last = nfull - 1;
-        Blk even, odd;
-        load(even, wave);
-        for (int jb = wave;; jb += 2 * GW) {
-            load(odd, min(jb + GW, last));
-            __builtin_amdgcn_sched_barrier(0);
-            block(even, 16);
-            if (jb + GW > last) break;
-            load(even, min(jb + 2 * GW, last));
-            __builtin_amdgcn_sched_barrier(0);
-            block(odd, 16);
-            if (jb + 2 * GW > last) break;
+    auto all_blocks = [&]() __attribute__((always_inline)) {
+        if (wave < nfull) {
+            const int last = nfull - 1;
+            Blk even, odd;
+            load(even, wave);
+            for (int jb = wave;; jb += 2 * GW) {
+                load(odd, min(jb + GW, last));
+                __builtin_amdgcn_sched_barrier(0);
+                block(even, 16);
+                if (jb + GW > last) break;
+                load(even, min(jb + 2 * GW, last));
+                __builtin_amdgcn_sched_barrier(0);
+                block(odd, 16);
+                if (jb + 2 * GW > last) break;
+            }
         }
-    }
-    if (nfull * 16 < H && wave == nfull % GW) {
-        Blk tail;
-        load_masked(tail, nfull);
-        block(tail, H - nfull * 16);
-    }
+        if (nfull * 16 < H && wave == nfull % GW) {
+            Blk tail;
+            load_masked(tail, nfull);
+            block(tail, H - nfull * 16);
+        }
+    };
 
-    l_run += __shfl_xor(l_run, 16, 64);
-    l_run += __shfl_xor(l_run, 32, 64);
     // Across the wavefronts that had keys.  Their weights and the denominator once per head: while every output element worked
     // them out for itself this part took a third of a call of few keys (f16 2 x 44 x 4 x 128 7.4 -> 5.5 us, fp32 32 x 16 x 64 x
     // 128 9.1 -> 7.7 us), which made those slower than the plain kernel (5.0 us; in fp32 with at most 24 keys of 128 it still
     // is by up to 15 %).
     const int active = min(GW, (H + 15) / 16);
-    if (q == 0) {
-        wave_max[wave * 16 + c] = m_run;
-        wave_sum[wave * 16 + c] = l_run;
-    }
-    if (wave < active) {
+    // Relative to a maximum that is still to rise, sums of very large values of V can pass the type's range although the result does
+    // not.  Where any sum is not finite, the keys are gone through once more with the heads' maxima known.
+    for (bool again = false;; again = true) {
+        all_blocks();
+        l_run += __shfl_xor(l_run, 16, 64);
+        l_run += __shfl_xor(l_run, 32, 64);
+        float bad = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+        for (int j = 0; j < VW; ++j)
 #pragma unroll
-            for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * D + VW * c + j] = acc[j][e];
+            for (int e = 0; e < 4; ++e) bad = not_finite(acc[j][e], bad);
+        const bool any = __builtin_amdgcn_ballot_w64(bad != bad) != 0;
+        if (lane == 0) wave_bad[wave] = any ? 1.f : 0.f;
+        if (q == 0) {
+            wave_max[wave * 16 + c] = m_run;
+            wave_sum[wave * 16 + c] = l_run;
+        }
+        if (wave < active) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * D + VW * c + j] = acc[j][e];
+        }
+        __syncthreads();
+        if (again || __builtin_amdgcn_ballot_w64(wave_bad[lane % GW] != 0.f) == 0) break;
+        m_run = -__builtin_inff();
+        for (int w = 0; w < active; ++w) m_run = fmaxf(m_run, wave_max[w * 16 + c]);
+        l_run = 0.f;
+#pragma unroll
+        for (int j = 0; j < VW; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();  // everyone has read the maxima
     }
-    __syncthreads();
     if (tid < 16 * GW) {
         const int head = tid & 15, mine = tid >> 4;
         float gmax = -__builtin_inff();
@@ -222,7 +244,7 @@ template <typename S, int D>
 static hipError_t launch_gqa_general_as(const AttentionCall& c) {
     typedef typename S::elem E;
     dim3 grid((c.G + kGqaGeneralHeads - 1) / kGqaGeneralHeads, c.B), block(GW * 64);
-    constexpr size_t lds = ((size_t)GW * 16 * (D + 3) + 16) * sizeof(float);
+    constexpr size_t lds = ((size_t)GW * 16 * (D + 3) + 16 + GW) * sizeof(float);
     auto kern = gqa_general_kernel<S, D>;
     static std::atomic<uint64_t> opted{0};
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;

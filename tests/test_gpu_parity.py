@@ -102,6 +102,47 @@ def test_softmax_any_shape_masked_and_non_finite(P, dtype):
                                atol=1e-5 if dtype == pi.F32 else 2.5e-3, equal_nan=True)
 
 
+# Very large values of W, or of V, whose weights vanish beside a maximum that comes later: sums relative to the maximum so far
+# pass the type's range, the result does not.  An infinity with a weight of its own stays one.
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
+@pytest.mark.parametrize("M,K,N", [(20, 301, 67), (33, 2001, 515), (8001, 97, 259), (700, 1001, 1283)])
+def test_softmax_any_shape_large_values_before_the_maximum(P, dtype, M, K, N):
+    import torch
+    from gpu_util import torch_dtype
+    gen = torch.Generator().manual_seed(8)
+    X, W = torch.randn(M, K, generator=gen).to(torch_dtype(dtype)), torch.randn(K, N, generator=gen).to(torch_dtype(dtype))
+    X[:, K - 3] = 150.0
+    W[:K // 2] = 3e38
+    X[5, 0], W[0, 7] = 149.0, float("inf")
+    Y = torch.empty(M, N, dtype=X.dtype, device="cuda")
+    P.prism_softmax_matmul(X.cuda(), W.cuda(), Y)
+    assert P.prism_plan(P.PRISM_OP_SOFTMAX_MATMUL, M, K, N, DTYPE_CODE[dtype])["path"] == P.PRISM_PATH_SIMPLE
+    ref = torch.softmax(X.double(), -1) @ W.double()
+    Y = Y.double().cpu()
+    # (a weight that is zero in fp32 meets the infinity in every row of its column but row 5)
+    assert Y[5, 7] == float("inf") and bool(torch.isfinite(Y[:, :7]).all()) and bool(torch.isfinite(Y[:, 8:]).all())
+    keep = torch.ones(N, dtype=torch.bool)
+    keep[7] = False
+    torch.testing.assert_close(Y[:, keep], ref[:, keep], rtol=2e-5 if dtype == pi.F32 else 4e-3, atol=1e-5 if dtype == pi.F32 else 4e-3)
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
+@pytest.mark.parametrize("G,H,D", [(5, 200, 64), (17, 333, 128), (16, 40, 64)])
+def test_attention_fp32_kernel_large_values_before_the_maximum(P, dtype, G, H, D):
+    import torch
+    from gpu_util import torch_dtype
+    gen = torch.Generator().manual_seed(9)
+    Q, K, V = (torch.randn(2, n, D, generator=gen).to(torch_dtype(dtype)) for n in (G, H, H))
+    Q[:] = 1.0
+    K[:, H - 2] = 4.0
+    V[:, :H // 2] = -3e38
+    O = torch.empty_like(Q).cuda()
+    P.prism_gqa_decode_attention(Q.cuda(), K.cuda(), V.cuda(), O)
+    assert P.prism_attention_plan(2, G, H, D, DTYPE_CODE[dtype])["path"] == P.PRISM_PATH_SIMPLE
+    ref = torch.softmax(Q.double() @ K.double().transpose(1, 2), -1) @ V.double()
+    torch.testing.assert_close(O.double().cpu(), ref, rtol=2e-5 if dtype == pi.F32 else 4e-3, atol=1e-5 if dtype == pi.F32 else 4e-3)
+
+
 # Shallow K: a few wavefronts on the narrowest tile, fewer K-blocks than wavefronts, or everything through LDS.
 @pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
 @pytest.mark.parametrize("M,K,N,gated,form", [(300, 5, 515, False, (16, 16, 128)), (301, 33, 515, True, (16, 16, 128)),

@@ -1093,6 +1093,7 @@ def test_two_streams_with_workspaces_of_their_own_run_split_k_calls_at_the_same_
             for i, s in enumerate(streams):
                 X, g, W = dev[i]
                 Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+                s.wait_stream(torch.cuda.current_stream())  # the fill comes before the call's stores
                 P.prism_rmsnorm_matmul(X, g, W, Y, stream=s)
                 outs[i].append(Y)
         torch.cuda.synchronize()

@@ -119,12 +119,13 @@ PRISM_ERR_WORKSPACE = 3
 
 
 def _load_marshal():
-    """The native route of ordinary calls (csrc/marshal.cpp); None where there is no torch to take tensors from."""
+    """The native route of ordinary calls (csrc/marshal.cpp); None where there is no torch to take tensors from, or no module
+    for this interpreter: every call then takes the general route."""
     try:
         import torch
+        from . import _marshal
     except ImportError:
         return None
-    from . import _marshal
     _marshal.setup(torch.Tensor, torch.nn.Parameter, torch.float32, torch.bfloat16, torch.float16,
                    getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
     return _marshal

@@ -1,4 +1,10 @@
 """The native route of ordinary calls from Python: the same results as the general route, the same refusals."""
+import importlib.util
+import os
+import subprocess
+import sys
+import sysconfig
+
 import pytest
 import torch
 
@@ -109,3 +115,41 @@ def test_calls_that_are_not_the_native_routes_keep_their_errors(P, name):
     t["X"] = t["X"][0]
     with pytest.raises(ValueError, match="unpack"):
         call(t)
+
+
+def test_the_package_works_without_the_native_module(repo_root):
+    """The module only shortens calls: where it was not built the general route takes them."""
+    code = ("import sys; sys.modules['paper_2604_15272_amd._marshal'] = None\n"
+            "import paper_2604_15272_amd as P; from paper_2604_15272_amd import binding\n"
+            "assert binding._native is None and P.prism_version() >= 200")
+    res = subprocess.run([sys.executable, "-c", code], cwd=repo_root, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+
+
+def test_the_library_is_built_without_pythons_headers(repo_root, monkeypatch, tmp_path):
+    spec = importlib.util.spec_from_file_location("_prism_build_for_test",
+                                                  os.path.join(repo_root, "paper_2604_15272_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    assert os.path.basename(build.MARSHAL).startswith("_marshal.cpython-")  # found by the interpreter it is for, no other
+    monkeypatch.setattr(sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_marshal() is None
+    calls = []
+    monkeypatch.setattr(build, "build_marshal", lambda: calls.append("marshal"))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libprism.so"))
+
+    def compiler(cmd, **kw):
+        calls.append(os.path.basename(cmd[0]))
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+
+    monkeypatch.setattr(build.subprocess, "run", compiler)
+    assert build.build_library() == build.LIB and calls == [os.path.basename(build.hipcc_path())]
+
+
+@pytest.mark.gpu
+def test_the_native_route_is_the_one_that_runs(P):
+    from paper_2604_15272_amd import binding
+    assert binding._native is not None
+    t = _tensors("cuda")
+    assert binding._native.product(*binding._SOFTMAX, t["X"], None, t["W1"], None, t["Y"], 0.0) == 0

@@ -6,6 +6,7 @@ Bars (stated by the benchmark spec): |y - yhat| <= 1e-5 (|yhat| + 1) for fp32
 import numpy as np
 import pytest
 
+import fp32_forms
 import prism_inputs as pi
 from gpu_util import (DTYPE_CODE, assert_parity, run_gpu, run_gpu_attention, run_gpu_softmax, run_oracle_attention,
                       run_oracle_softmax, run_gpu_variant, run_oracle, run_oracle_variant, worst_error)
@@ -62,8 +63,7 @@ def test_simple_bf16_unaligned_shapes(P, M, K, N, gated):
     _case(P, pi.BF16, M, K, N, gated, seed=200 + M, expect_path=P.PRISM_PATH_SIMPLE)
 
 
-# On 256 compute units these take every form of the kernel (16 or 32 rows; 16, 64 or 128 columns), with ragged rows, a
-# last K-block that is not full, a column group shifted back from the right edge, and the smallest width.
+# Ragged rows, a last K-block that is not full, a column group shifted back from the right edge, and the smallest width.
 @pytest.mark.parametrize("dtype", [pi.F32, pi.BF16, pi.F16])
 @pytest.mark.parametrize("gated", [False, True])
 @pytest.mark.parametrize("M,K,N", [(3, 37, 3), (16, 500, 1003), (17, 290, 2050), (64, 2047, 2048), (33, 65, 515),
@@ -141,6 +141,77 @@ def test_attention_fp32_kernel_large_values_before_the_maximum(P, dtype, G, H, D
     assert P.prism_attention_plan(2, G, H, D, DTYPE_CODE[dtype])["path"] == P.PRISM_PATH_SIMPLE
     ref = torch.softmax(Q.double() @ K.double().transpose(1, 2), -1) @ V.double()
     torch.testing.assert_close(O.double().cpu(), ref, rtol=2e-5 if dtype == pi.F32 else 4e-3, atol=1e-5 if dtype == pi.F32 else 4e-3)
+
+
+# Every form of the fp32 kernels, the plan's as well as the result's.
+@pytest.mark.parametrize("dtype,gated,form,shape", [(dt, g, f, s) for dt in (pi.F32, pi.BF16, pi.F16) for g in (False, True)
+                                                    for f, s in fp32_forms.PRODUCTS[g, dt == pi.F32]])
+def test_every_form_of_the_fp32_products(P, dtype, gated, form, shape):
+    plan = P.prism_plan(int(gated), *shape, DTYPE_CODE[dtype])
+    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
+    _case(P, dtype, *shape, gated, seed=310 + shape[1], expect_path=P.PRISM_PATH_SIMPLE)
+
+
+@pytest.mark.parametrize("dtype,form,shape", [(dt, f, s) for dt in (pi.F32, pi.BF16, pi.F16)
+                                              for f, s in fp32_forms.SOFTMAX[dt == pi.F32]])
+def test_every_form_of_the_fp32_softmax(P, dtype, form, shape):
+    plan = P.prism_plan(P.PRISM_OP_SOFTMAX_MATMUL, *shape, DTYPE_CODE[dtype])
+    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
+    _softmax_case(P, dtype, *shape, seed=320 + shape[1], expect_path=P.PRISM_PATH_SIMPLE)
+
+
+# Memory right past what a call owns, full of infinities and NaNs: rows of the products' operands that follow the last K value
+# and columns that follow the last one are the next row's, so what lies past the end is put there by hand.
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("M,K,N", [(5, 37, 67), (1999, 37, 1023), (1010, 545, 515), (40, 290, 2050), (4093, 159, 259)])
+def test_products_of_any_shape_read_nothing_past_their_operands(P, dtype, gated, M, K, N):
+    import torch
+    from gpu_util import torch_dtype
+    gen = torch.Generator().manual_seed(330 + K)
+
+    def guarded(*shape, std=1.0):
+        n = shape[0] * (shape[1] if len(shape) > 1 else 1)
+        t = torch.empty(n + 4096, dtype=torch_dtype(dtype), device="cuda")
+        t[:n] = (torch.randn(n, generator=gen) * std).to(t.dtype).cuda()
+        t[n::2], t[n + 1::2] = float("inf"), float("nan")
+        return t[:n].view(*shape)
+
+    X, g, W1, W2 = guarded(M, K), guarded(K), guarded(K, N, std=K ** -0.5), guarded(K, N, std=K ** -0.5)
+    Y = torch.full((M + 1, N), 7.0, dtype=X.dtype, device="cuda")
+    if gated:
+        P.prism_rmsnorm_glu(X, g, W1, W2, Y[:M], eps=1e-6)
+    else:
+        P.prism_rmsnorm_matmul(X, g, W1, Y[:M], eps=1e-6)
+    assert P.prism_plan(int(gated), M, K, N, DTYPE_CODE[dtype])["path"] == P.PRISM_PATH_SIMPLE
+    Xd = X.double()
+    Nd = Xd * torch.rsqrt(Xd.square().mean(-1, keepdim=True) + 1e-6) * g.double()
+    ref = (Nd @ W1.double()) * (Nd @ W2.double()) if gated else Nd @ W1.double()
+    # (fp32 throughout; bf16 rounds the output alone, by 2^-9 of it)
+    torch.testing.assert_close(Y[:M].double(), ref, rtol=2e-5 if dtype == pi.F32 else 2.0 ** -8, atol=2e-5)
+    assert bool((Y[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("M,K,N", [(20, 101, 67), (1999, 37, 1023), (1010, 545, 515)])
+def test_any_shape_infinities_of_w_stay_in_their_column(P, gated, M, K, N):
+    """Also in the last columns, whose group overlaps its neighbour's, and in the last row of W, in a K-block that is not full."""
+    import torch
+    gen = torch.Generator().manual_seed(340)
+    X, W1, W2 = torch.randn(M, K, generator=gen), torch.randn(K, N, generator=gen), torch.randn(K, N, generator=gen)
+    bad = [0, N // 2, N - 4, N - 1]
+    for i, n in enumerate(bad):
+        (W2 if gated and i % 2 else W1)[K - 1 if i != 1 else 0, n] = float("inf") if i < 2 else float("nan")
+    Y = torch.empty(M, N, device="cuda")
+    if gated:
+        P.prism_rmsnorm_glu(X.cuda(), None, W1.cuda(), W2.cuda(), Y)
+    else:
+        P.prism_rmsnorm_matmul(X.cuda(), None, W1.cuda(), Y)
+    finite = torch.isfinite(Y).cpu()
+    assert not bool(finite[:, bad].any())
+    rest = torch.ones(N, dtype=torch.bool)
+    rest[bad] = False
+    assert bool(finite[:, rest].all())
 
 
 # Shallow K: a few wavefronts on the narrowest tile, fewer K-blocks than wavefronts, or everything through LDS.

@@ -683,3 +683,23 @@ def test_fp32_forms_of_shallow_k(P):
         assert form(2, f16, 1000, 36, 200) == (16, 16, 256)
     finally:
         P.prism_diag_set_cu_count(0)
+
+
+def test_the_parity_cases_take_every_form_of_the_fp32_kernels(P):
+    import fp32_forms as ff
+    P.prism_diag_set_cu_count(256)
+    try:
+        for (gated, wide), cases in ff.PRODUCTS.items():
+            for dt in ([P.PRISM_F32] if wide else [P.PRISM_BF16, P.PRISM_F16]):
+                for form, shape in cases:
+                    p = P.prism_plan(int(gated), *shape, dt)
+                    assert p["path"] == P.PRISM_PATH_SIMPLE and (p["tile_m"], p["tile_n"], p["block"]) == form, (gated, dt, shape, p)
+            assert {f[:2] for f, _ in cases} == ff.COMPILED_PRODUCTS[gated, wide]
+        for wide, cases in ff.SOFTMAX.items():
+            for dt in ([P.PRISM_F32] if wide else [P.PRISM_BF16, P.PRISM_F16]):
+                for form, shape in cases:
+                    p = P.prism_plan(P.PRISM_OP_SOFTMAX_MATMUL, *shape, dt)
+                    assert p["path"] == P.PRISM_PATH_SIMPLE and (p["tile_m"], p["tile_n"], p["block"]) == form, (dt, shape, p)
+            assert {f[:2] for f, _ in cases} == ff.COMPILED_SOFTMAX[wide]
+    finally:
+        P.prism_diag_set_cu_count(0)

@@ -180,15 +180,15 @@ void choose_prefill_tile(bool gated, int64_t M, int64_t N, int variant, int* bm,
 //
 // One weight matrix: 3000 calls of 17 to 512 rows against K x N from 64 x 64 to 14336 x 36000 (at most 1.2e8 weights, rotated
 // through HBM), every candidate forced: the choice is 0.95 % above the best on average (11 % on the worst hundredth), and
-// 1.1 % (17 %) on 1200 other calls; of those, 0.3 % are more than 2 % slower than the choice by the constants that were here
-// first (a regret of 2.2 %), the worst 11 %.  (Constants fitted to 110 calls with K from 512 on, in between, left out what a
+// 1.1 % (17 %) on 1200 other calls, 0.4 % on 1000 of round sizes (K and N from 1024 to 14336); of all, 0.6 % are more than 2 %
+// slower than the choice by the constants that were here first (a regret of 2.2 %), the worst 13 %.  (Constants fitted to 110 calls with K from 512 on, in between, left out what a
 // round of workgroups costs: 237 x 64 x 16064 7.2 -> 17.5 us, 398 x 704 x 4672 13.6 -> 20.2 us, one call in ten 5 % or more.)
 //   multi-row kernel, S K-slices, z row blocks, microseconds:
 //     loop  = (1 + 1.3 x further rounds of workgroups) x (start + reduction 5.0 / 6.4 (32 / 64 rows) + 0.02 / 0.24 per
 //             K-block of a slice; X through LDS: 1.3 / 7.0 + 0.19 / 0.23 per K-block, in trips of sixteen)
 //     HBM   = W at 6.5 TB/s, and for every further row block a part of that again: 1.0 / 0.25 of it in several rounds, 0.64
-//             / 1.0 in one, half where all row blocks of a tile run on the same XCD (column tiles x slices a multiple of
-//             eight); + the start
+//             / 1.0 in one, 0.58 / 0.53 where all row blocks of a tile run on the same XCD (column tiles x slices a multiple
+//             of eight); + the start
 //     L2    = W once per row block and X once per column tile at 15 TB/s; + the start
 //     the longest of the three, and with S > 1 the exchange, 2.0 + 0.13 x S x row groups
 //   prefill kernel: (start + K steps x the step of the tile) x the rounds (x 0.5 for 128-row and smaller tiles, two of
@@ -246,7 +246,7 @@ RowsEstimate rows_estimate(int rg, bool gated, int64_t M, int64_t K, int64_t N, 
         struct C {
             double start, per_k, start_lds, per_k_lds, again_rounds, again_xcd, again;
         };
-        static const C consts[2] = {{5.0, 0.02, 1.3, 0.19, 1.0, 0.52, 0.64}, {6.4, 0.24, 7.0, 0.23, 0.25, 0.53, 1.0}};
+        static const C consts[2] = {{5.0, 0.02, 1.3, 0.19, 1.0, 0.58, 0.64}, {6.4, 0.24, 7.0, 0.23, 0.25, 0.53, 1.0}};
         const C& k = consts[rg / 2 - 1];
         const int64_t S = rows_slices(wgs1, kblocks, cus), slice = (kblocks + S - 1) / S, rounds = (wgs1 * S + cus - 1) / cus;
         const double loop = rows_x_through_lds(rg, slice) ? k.start_lds + k.per_k_lds * (double)((slice + 15) / 16 * 16)
@@ -316,12 +316,12 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     const double t32 = ok32 ? r32.us : 1e300, t64 = ok64 ? r64.us : 1e300;
     if (rows_model_fits(gated, K, N) && ok32 && K <= 4 * kDecodeKBlock && n_tiles * z32 <= cus) return 2;
     if (pf <= t32 && pf <= t64) return 0;
-    // Estimates within 11 %: 32 rows where only their partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64
+    // Estimates within 14 %: 32 rows where only their partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64
     // rows need 8.5 MB, four of 32 rows half of that; 22.6 / 23.2 us).
     auto fits_scratch = [&](const RowsEstimate& r) {
         return r.S == 1 || PRISM_WORKSPACE_HEADER_BYTES + (double)r.S * (gated ? 2 : 1) * (double)M * (double)N * 4.0 <= PRISM_STATIC_SCRATCH_BYTES - 65536.0;
     };
-    if (t32 <= 1.11 * t64 && fits_scratch(r32) && !fits_scratch(r64)) return 2;
+    if (t32 <= 1.14 * t64 && fits_scratch(r32) && !fits_scratch(r64)) return 2;
     return t32 <= t64 ? 2 : 4;
 }
 

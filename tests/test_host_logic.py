@@ -656,6 +656,7 @@ def test_mid_size_calls_of_shallow_k_and_wide_n_take_the_faster_kernel(P):
         assert rows(54, 4592, 9064) == many         # 39.2 / 27.8 / 56.5
         assert rows(30, 64, 128) == few             # 4.2 / 6.1 / 4.2
         assert rows(128, 4096, 4096) == many        # 20.9 / 19.5 / 50.9
+        assert rows(80, 4096, 4096) == many         # 20.4 / 18.0 / 50.3
         assert rows(64, 4096, 4096) == few          # 15.8 / 17.2 / 51.0
         assert rows(512, 2048, 2048) == few         # 12.1 / 16.4 / 20.1
     finally:

@@ -227,9 +227,10 @@ hipError_t launch_softmax_rows_16bit(const SoftmaxCall& c, bool f16) {
 // row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
 // beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
 // The kernel this replaces (8 rows x 256 columns, one thread per column, two passes over X) was bound by its serial loads:
-// fp32 1624 x 3008 x 352 794 us, now 81 us.
-// Bound now: the fp32 matrix rate (fp32 4096 x 4096 x 128: 68 us, 63 TFLOP/s beside 17e6 exponentials per column tile), or,
-// with few workgroups, the chain of a wavefront's blocks.
+// fp32 1624 x 3008 x 352 794 us, now 76 us.
+// Bound now: nothing single.  fp32 4096 x 4096 x 128 takes 62 us, 69 of 157 TFLOP/s: the matrix cores are busy 46 % of the cycles
+// in which a compute unit has a workgroup, beside 17e6 exponentials for every column tile and operands straight from the
+// caches.  With few workgroups it is the chain of a wavefront's blocks.
 template <typename S, int RG, int VW>
 __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_general_kernel(const typename S::elem* __restrict__ X,
                                                                             const typename S::elem* __restrict__ W,
@@ -370,9 +371,10 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
     }
     store_group(0);
     __syncthreads();
-    // The wavefronts' weights and the denominators: once per row where threads have several outputs (bf16 4000 x 513 x 129
-    // 28.7 -> 27.3 us), else by each output for itself (fp32 64 x 256 x 128 4.7 us, 6.3 us once per row).
-    constexpr bool PER_ROW = VW > 1;
+    // The wavefronts' weights and the denominators: once per row where a thread has four outputs (bf16 4000 x 513 x 129
+    // 28.7 -> 27.3 us), else by each output for itself (two: fp32 1624 x 3008 x 352 74.9 us, 75.8 us once per row; one: fp32 64 x
+    // 256 x 128 4.7 / 6.3 us).
+    constexpr bool PER_ROW = RG * VW >= 8;
     auto row_max = [&](int row) __attribute__((always_inline)) {
         float m = -__builtin_inff();
         for (int w = 0; w < nw; ++w) m = fmaxf(m, wave_max[w * (16 * RG) + row]);

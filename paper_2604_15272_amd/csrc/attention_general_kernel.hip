@@ -8,10 +8,11 @@
 // 4 q + i (the order of K within a block is free): nothing is rearranged in between.  The maximum over a block's keys is four
 // values in a lane and two exchanges.  Each wavefront keeps a running maximum per head; the partials meet in LDS at the end.
 //
-// What bounds it: the fp32 matrix rate of the compute units that have a batch entry (16 keys of 16 heads: 4 D products of
-// 512 operations a clock).  One thread per key and per column (the plain kernel) waited for its loads: f16 32 x 8 x 5001 x 64 376 ->
-// 65 us, fp32 32 x 8 x 5000 x 128 431 -> 107 us, fp32 2 x 8 x 2048 x 128 102 -> 47 us, one entry of 16384 keys (16 heads, f16, D = 64)
-// 640 -> 198 us, fp32 64 x 1 x 2500 x 64 195 -> 32 us; errors against 64 bits of fp32 storage are less than half of what they were.
+// What bounds it: the compute units that have a batch entry, one per sixteen heads: their matrix cores are busy 52 to 58 % of
+// their cycles (f16 32 x 8 x 5001 x 64, 11 % of the units at work: 66 us, its products alone 33 us), the rest is the chain of a
+// block's maximum, exponentials and rescaling.  One thread per key and per column (the plain kernel) waited for its loads: on
+// changing keys that case 506 -> 66 us, fp32 32 x 8 x 5000 x 128 622 -> 127 us, fp32 2 x 8 x 2048 x 128 174 -> 48 us, one entry of
+// 16384 keys (16 heads, f16, D = 64) 1175 -> 198 us, fp32 64 x 1 x 2500 x 64 297 -> 35 us; errors against 64 bits of fp32 storage are less than half of what they were.
 #include "any_shape.h"
 #include "device_utils.h"
 #include "prism_internal.h"

@@ -118,9 +118,11 @@ __global__ __launch_bounds__(NT) void decode_rows_kernel(const uint16_t* __restr
         // way while a block is multiplied (two areas per wavefront, two register sets of W).  The one wait that the
         // compiler does not place, for X in LDS, counts instructions: only the youngest set of W (its eight rows and the
         // gain) may still be in flight, and every group of loads is fenced so that it stays in the order written.
-        // Before (four blocks of X at a time, a full wait before each block) and now: 512 x 4096 x 4096 29.5 -> 27.0 us, 128 x
-        // 4096 x 4096 17.2 -> 15.2 us (as 32 rows), 200 x 4096 x 4096 23.2 -> 20.9 us.  What bounds it now: W and X through
-        // the L2, once per row block (18 TB/s over the chip at 200 x 4096 x 4096).
+        // Before (four blocks of X at a time, a full wait before each block) and now, on one set of weights: 512 x 4096 x 4096
+        // 29.5 -> 27.0 us, 128 x 4096 x 4096 17.2 -> 15.2 us (as 32 rows, which the dispatcher does not take: with weights from
+        // HBM 20.9 us, 64 rows 19.5), 200 x 4096 x 4096 23.2 -> 20.9 us (on changing weights 21.0 -> 20.4).  What bounds it
+        // now: W and X through the L2, once per row block (18 TB/s over the chip at 200 x 4096 x 4096); the matrix cores are busy
+        // 21 to 30 % of a busy compute unit's cycles.
         typedef __attribute__((address_space(3))) void* lds_ptr;
         constexpr int AREA = RG * 128;  // 16-byte slots of a pair's X
         u32x4* xs_lane = (u32x4*)lds + (size_t)wave * (2 * AREA);

@@ -8,8 +8,9 @@
 // while the present one is multiplied.  Two wavefronts per SIMD: the operand reads of one run under the products of the
 // other.  Same case: 74 us, 115 TFLOP/s;
 // 4096 x 1024 x 1024 94 -> 71 us; 512 x 1024 x 4096 53 -> 42 us with 64 rows.
-// What bounds it: the fp32 matrix rate (91 % of it while it runs: 65 us per 1024 K values of a 128-row tile, beside 59
-// at 157 TFLOP/s), and about 7 us of launch, first stage and last reduction per call.
+// What bounds it: the fp32 matrix rate (65 us per 1024 K values of a 128-row tile, 84 % of the 54.6 us at 157 TFLOP/s;
+// counted, the matrix cores are busy 76 to 81 % of the cycles in which a compute unit has a workgroup, without bank
+// conflicts), and about 7 us of launch, first stage and last reduction per call.
 // (With the next stage requested at the start of a trip and stored at its end the case took 86 us: every wavefront of the
 // compute unit then waits for memory and stores at the same time.)
 //

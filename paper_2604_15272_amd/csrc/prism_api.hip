@@ -317,7 +317,8 @@ int decode_row_groups(bool gated, int64_t M, int64_t K, int64_t N) {
     if (rows_model_fits(gated, K, N) && ok32 && K <= 4 * kDecodeKBlock && n_tiles * z32 <= cus) return 2;
     if (pf <= t32 && pf <= t64) return 0;
     // Estimates within 14 %: 32 rows where only their partial sums fit the static scratch (64 x 8192 x 4096: eight slices of 64
-    // rows need 8.5 MB, four of 32 rows half of that; 22.6 / 23.2 us).
+    // rows need 8.5 MB, four of 32 rows half of that; 22.6 / 23.2 us; 64 x 11008 x 4096 26.8 / 27.7 us; where 64 rows gain more, as
+    // for 64 x 14336 x 4096, 30.7 / 33.7 us, they stay).
     auto fits_scratch = [&](const RowsEstimate& r) {
         return r.S == 1 || PRISM_WORKSPACE_HEADER_BYTES + (double)r.S * (gated ? 2 : 1) * (double)M * (double)N * 4.0 <= PRISM_STATIC_SCRATCH_BYTES - 65536.0;
     };
@@ -378,8 +379,9 @@ Choice resolve_choice(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_dtyp
 //     narrowest tile with 2 wavefronts (4 beyond K = 64); below 0.4 units the estimate above is as good.
 //   softmax: one wavefront from 2 units on (64 columns from 8 on, and that up to K = 320), 2 from 1 on, else 4 (fp32 15281 x 2 x 499
 //     31 / 104, bf16 7197 x 22 x 1602 40 / 135, fp32 6844 x 16 x 394 16 / 44).
-// 3 to 4 % above the best form on average.  The kernels with one thread per column that were here before are still up to 20 %
-// faster for K < 8 with millions of outputs (gated bf16 2612 x 3 x 13370 82 / 100 us).
+// 3 to 4 % above the best form on average.  The kernels with one thread per column that were here before were still
+// up to 30 % faster for K < 16 and a gate, 20 % for the softmax and K < 6 (gated bf16 2612 x 3 x 13370 75 / 94 us, gated f16 197 x 7 x
+// 17532 16 / 21, softmax fp32 15281 x 2 x 499 26 / 31).
 bool shallow_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, GeneralForm* out) {
     const double units = (double)((N + 63) / 64) * (double)((M + 15) / 16) / (double)cu_count();
     if (K > (softmax && units >= 8.0 ? 320 : 128)) return false;

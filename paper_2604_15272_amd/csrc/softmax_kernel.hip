@@ -227,8 +227,8 @@ hipError_t launch_softmax_rows_16bit(const SoftmaxCall& c, bool f16) {
 // row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
 // beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
 // The kernel this replaces (8 rows x 256 columns, one thread per column, two passes over X) was bound by its serial loads:
-// fp32 1624 x 3008 x 352 794 us, now 76 us.
-// Bound now: nothing single.  fp32 4096 x 4096 x 128 takes 62 us, 69 of 157 TFLOP/s: the matrix cores are busy 46 % of the cycles
+// fp32 1624 x 3008 x 352 794 us, now 75 to 81 us.
+// Bound now: nothing single.  fp32 4096 x 4096 x 128 takes 62 to 69 us, 62 to 69 of 157 TFLOP/s: the matrix cores are busy 46 % of the cycles
 // in which a compute unit has a workgroup, beside 17e6 exponentials for every column tile and operands straight from the
 // caches.  With few workgroups it is the chain of a wavefront's blocks.
 template <typename S, int RG, int VW>

@@ -379,13 +379,22 @@ Choice resolve_choice(prism_op_t op, int64_t M, int64_t K, int64_t N, prism_dtyp
 //     narrowest tile with 2 wavefronts (4 beyond K = 64); below 0.4 units the estimate above is as good.
 //   softmax: one wavefront from 2 units on (64 columns from 8 on, and that up to K = 320), 2 from 1 on, else 4 (fp32 15281 x 2 x 499
 //     31 / 104, bf16 7197 x 22 x 1602 40 / 135, fp32 6844 x 16 x 394 16 / 44).
+// 16-bit storage: sixteen columns are 32 bytes of a row of W, so the narrow tile loses where W is most of the traffic, and the
+// estimate's wider forms stay (200 more calls of 1 to 128 rows; us, narrow tile / the estimate's form):
+//   products beyond K = 64 from where the estimate has four wavefronts, 6 units, with a gate 1.5 and up to 32 rows (bf16
+//     46 x 81 x 57820 30 / 21, gated 10 x 116 x 118608 43 / 30; below that 23 x 87 x 40583 16 / 21, gated 60 x 97 x 14967 13.9 / 14.7); so does
+//     fp32 from 4 units beyond K = 32, with a gate 64 (74 x 86 x 47045 28 / 21, 2 x 38 x 78564 6.8 / 5.8, gated 7 x 123 x 85873 28 / 22);
+//   softmax from 160000 elements of W on, below 4 units for up to 16 rows and K > 32, else below 2, at K <= 64 below 1 (bf16
+//     2 x 112 x 10492 7.6 / 5.3, 8 x 45 x 29924 8.0 / 7.0, 42 x 109 x 5037 8.2 / 6.8; smaller 56 x 101 x 1521 5.3 / 6.2).
 // 3 to 4 % above the best form on average.  The kernels with one thread per column that were here before were still
 // up to 30 % faster for K < 16 and a gate, 20 % for the softmax and K < 6 (gated bf16 2612 x 3 x 13370 75 / 94 us, gated f16 197 x 7 x
 // 17532 16 / 21, softmax fp32 15281 x 2 x 499 26 / 31).
-bool shallow_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, GeneralForm* out) {
+bool shallow_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_t N, prism_dtype_t dtype, GeneralForm* out) {
     const double units = (double)((N + 63) / 64) * (double)((M + 15) / 16) / (double)cu_count();
     if (K > (softmax && units >= 8.0 ? 320 : 128)) return false;
+    const bool narrow_rows = dtype != PRISM_F32;
     if (softmax) {
+        if (narrow_rows && K * N >= 160000 && units < (M <= 16 && K > 32 ? 4.0 : (K > 64 ? 2.0 : 1.0))) return false;
         *out = GeneralForm{1, units >= 8.0 && N >= 4 ? 4 : 1, units >= 2.0 ? 1 : (units >= 1.0 ? 2 : 4)};
         return true;
     }
@@ -394,6 +403,8 @@ bool shallow_general_form(bool gated, bool softmax, int64_t M, int64_t K, int64_
         return true;
     }
     if (units < 0.4) return false;
+    if (narrow_rows && M < 128 && K > 64 && (gated ? units >= 1.5 && M <= 32 : units >= 6.0)) return false;
+    if (!narrow_rows && M < 128 && K > (gated ? 64 : 32) && units >= 4.0) return false;
     *out = GeneralForm{1, 1, K <= 64 ? 2 : 4};
     return true;
 }
@@ -404,7 +415,7 @@ GeneralForm choose_general_form(bool gated, bool softmax, int64_t M, int64_t K, 
     const bool wide = dtype == PRISM_F32;
     const double cus = (double)cu_count(), G = gated ? 2.0 : 1.0;
     GeneralForm best{1, 1, 8};
-    if (shallow_general_form(gated, softmax, M, K, N, &best)) {
+    if (shallow_general_form(gated, softmax, M, K, N, dtype, &best)) {
         if (N > (1 << 28)) best.waves = 1;  // the grid's threads are counted in 32 bits
         return best;
     }

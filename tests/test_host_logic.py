@@ -682,6 +682,15 @@ def test_fp32_forms_of_shallow_k(P):
         assert form(2, f32, 6844, 16, 394) == (16, 64, 64)        # 15 / 44
         assert form(2, f16, 382, 10, 3004) == (16, 16, 64)        # 9.9 / 20.3
         assert form(2, f16, 1000, 36, 200) == (16, 16, 256)
+        # few rows, wide W: the narrow tile reads too little of a row at a time (us, this form / the narrow tile)
+        assert form(2, bf16, 2, 112, 10492) == (16, 64, 512)      # 5.3 / 7.6
+        assert form(2, bf16, 8, 45, 29924) == (16, 128, 512)      # 7.0 / 8.0
+        assert form(2, bf16, 56, 101, 1521) == (16, 16, 256)      # 5.3, 6.2 in 64 columns
+        assert form(0, bf16, 46, 81, 57820) == (16, 128, 256)     # 21 / 30
+        assert form(0, bf16, 23, 87, 40583) == (16, 16, 256)      # 16, 21 in 128 columns
+        assert form(1, bf16, 10, 116, 118608) == (16, 128, 256)   # 30 / 43
+        assert form(0, f32, 74, 86, 47045) == (16, 64, 256)       # 21 / 28
+        assert form(1, f32, 7, 123, 85873) == (16, 64, 256)       # 22 / 28
     finally:
         P.prism_diag_set_cu_count(0)
 

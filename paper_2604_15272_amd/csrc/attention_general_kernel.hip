@@ -25,7 +25,7 @@ constexpr int GW = kGqaGeneralWaves;
 
 }  // namespace
 
-// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums, [GW][16] weights, [16] denominators, [GW] flags.
+// LDS: [GW][16][D] partial outputs, [GW][16] maxima, [GW][16] sums, [GW] flags.
 template <typename S, int D>
 __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::elem* __restrict__ Q,
                                                               const typename S::elem* __restrict__ K,
@@ -44,9 +44,7 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
     float* red = lds;
     float* wave_max = lds + GW * 16 * D;
     float* wave_sum = wave_max + GW * 16;
-    float* weight = wave_sum + GW * 16;
-    float* total = weight + GW * 16;
-    float* wave_bad = total + 16;
+    float* wave_bad = wave_sum + GW * 16;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -171,23 +169,27 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
         }
     };
 
-    // Across the wavefronts that had keys.  Their weights and the denominator once per head: while every output element worked
-    // them out for itself this part took a third of a call of few keys (f16 2 x 44 x 4 x 128 7.4 -> 5.5 us, fp32 32 x 16 x 64 x
-    // 128 9.1 -> 7.7 us), which made those slower than the plain kernel (5.0 us; in fp32 with at most 24 keys of 128 it still
-    // is by up to 15 %).
+    // Across the wavefronts that had keys.  Their weights are worked out once, in the lanes of each wavefront, not by every output
+    // element for itself: that took a quarter of a call of few keys (us, before -> now: f16 2 x 44 x 4 x 128 7.5 -> 5.6, fp32
+    // 32 x 16 x 64 x 128 9.1 -> 7.9, bf16 25 x 28 x 121 x 64 6.0 -> 5.9).  One to three heads have little to share and pay 0.1 to 0.3
+    // for the check of the sums: f16 11 x 2 x 164 x 64 5.7 -> 6.0, fp32 10 x 3 x 411 x 64 8.8 -> 9.0.
     const int active = min(GW, (H + 15) / 16);
+    // Lane (q, c) of every wavefront: maxima, weights and sums of head c in wavefronts q and q + 4.
+    static_assert(GW == 8 && D % 64 == 0, "four lanes a head, a wavefront's outputs are of one head");
+    float mx[2], weight[2], sum[2], gmax;
     // Relative to a maximum that is still to rise, sums of very large values of V can pass the type's range although the result does
     // not.  Where any sum is not finite, the keys are gone through once more with the heads' maxima known.
     for (bool again = false;; again = true) {
         all_blocks();
         l_run += __shfl_xor(l_run, 16, 64);
         l_run += __shfl_xor(l_run, 32, 64);
-        float bad = 0.f;
+        float bad[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < VW; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bad = not_finite(acc[j][e], bad);
-        const bool any = __builtin_amdgcn_ballot_w64(bad != bad) != 0;
+            for (int e = 0; e < 4; ++e) bad[e] = not_finite(acc[j][e], bad[e]);
+        const float all = (bad[0] + bad[1]) + (bad[2] + bad[3]);
+        const bool any = __builtin_amdgcn_ballot_w64(all != all) != 0;
         if (lane == 0) wave_bad[wave] = any ? 1.f : 0.f;
         if (q == 0) {
             wave_max[wave * 16 + c] = m_run;
@@ -200,44 +202,43 @@ __global__ __launch_bounds__(GW * 64) void gqa_general_kernel(const typename S::
                 for (int j = 0; j < VW; ++j) red[(wave * 16 + 4 * q + e) * D + VW * c + j] = acc[j][e];
         }
         __syncthreads();
-        if (again || __builtin_amdgcn_ballot_w64(wave_bad[lane % GW] != 0.f) == 0) break;
-        m_run = -__builtin_inff();
-        for (int w = 0; w < active; ++w) m_run = fmaxf(m_run, wave_max[w * 16 + c]);
+        const float flag = wave_bad[lane % GW];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool had = q + 4 * i < active;
+            mx[i] = had ? wave_max[(q + 4 * i) * 16 + c] : -__builtin_inff();
+            sum[i] = had ? wave_sum[(q + 4 * i) * 16 + c] : 0.f;
+        }
+        gmax = fmaxf(mx[0], mx[1]);
+        gmax = fmaxf(gmax, __shfl_xor(gmax, 16, 64));
+        gmax = fmaxf(gmax, __shfl_xor(gmax, 32, 64));
+        if (again || __builtin_amdgcn_ballot_w64(flag != 0.f) == 0) break;
+        m_run = gmax;
         l_run = 0.f;
 #pragma unroll
         for (int j = 0; j < VW; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         __syncthreads();  // everyone has read the maxima
     }
-    if (tid < 16 * GW) {
-        const int head = tid & 15, mine = tid >> 4;
-        float gmax = -__builtin_inff();
-        for (int w = 0; w < active; ++w) gmax = fmaxf(gmax, wave_max[w * 16 + head]);
-        float den = 0.f;
-        for (int w = 0; w < active; ++w) {
-            const float mw = wave_max[w * 16 + head];
-            // A wavefront with no key above -inf is relative to 0 and weighs nothing; a NaN in its sums stays one.
-            const float f = (mw == -__builtin_inff()) ? 0.f : expf(mw - gmax);
-            den = fmaf(f, wave_sum[w * 16 + head], den);
-            if (w == mine) weight[w * 16 + head] = f;
+    // A wavefront with no key above -inf is relative to 0 and weighs nothing; a NaN in its sums stays one.
+#pragma unroll
+    for (int i = 0; i < 2; ++i) weight[i] = (mx[i] == -__builtin_inff()) ? 0.f : expf(mx[i] - gmax);
+    auto of_head = [&](const float (&x)[2], int w, int head) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[w >> 2]), (w & 3) * 16 + head));
+    };
+#pragma unroll
+    for (int i = 0; i < 16 * D / (GW * 64); ++i) {
+        const int head = (wave * 64 + i * (GW * 64)) / D;  // the same for all lanes
+        if (g0 + head >= G) break;
+        const int o = tid + i * (GW * 64);
+        float v = 0.f, den = 0.f;
+#pragma unroll
+        for (int w = 0; w < GW; ++w) {
+            if (w >= active) break;
+            const float f = of_head(weight, w, head);
+            v = fmaf(f, red[w * 16 * D + o], v);
+            den = fmaf(f, of_head(sum, w, head), den);
         }
-        if (mine == 0) total[head] = den;
-    }
-    __syncthreads();
-    // A thread's outputs together: one after the other they would wait for the LDS in turn.
-    constexpr int PER = 16 * D / (GW * 64);
-    float v[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) v[i] = 0.f;
-    for (int w = 0; w < active; ++w)
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int o = tid + i * (GW * 64);
-            v[i] = fmaf(weight[w * 16 + o / D], red[w * 16 * D + o], v[i]);
-        }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int o = tid + i * (GW * 64), head = o / D;
-        if (g0 + head < G) O[((size_t)bi * G + g0) * D + o] = S::narrow(v[i] / total[head]);
+        O[((size_t)bi * G + g0) * D + o] = S::narrow(v / den);
     }
 }
 
@@ -245,7 +246,7 @@ template <typename S, int D>
 static hipError_t launch_gqa_general_as(const AttentionCall& c) {
     typedef typename S::elem E;
     dim3 grid((c.G + kGqaGeneralHeads - 1) / kGqaGeneralHeads, c.B), block(GW * 64);
-    constexpr size_t lds = ((size_t)GW * 16 * (D + 3) + 16 + GW) * sizeof(float);
+    constexpr size_t lds = ((size_t)GW * 16 * (D + 2) + GW) * sizeof(float);
     auto kern = gqa_general_kernel<S, D>;
     static std::atomic<uint64_t> opted{0};
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;

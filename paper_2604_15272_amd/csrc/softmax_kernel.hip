@@ -421,7 +421,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
             }
             // Relative to a maximum that was still to rise, sums of very large values of W can pass the type's range although the
             // result does not: such an output is summed once more, one product after the other, with the maximum known.
-            if (fabsf(v) > kFloatMax || v != v) {
+            if (__builtin_expect(!(fabsf(v) <= kFloatMax), 0)) {
                 const float shift = row_max(16 * r + row);
                 if (den <= kFloatMax && shift > -__builtin_inff()) {  // (else a NaN or an infinity of X: the output is a NaN)
                     v = 0.f;

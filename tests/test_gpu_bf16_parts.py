@@ -157,3 +157,37 @@ def test_attention_in_parts_infinities_of_v(dtype):
     Vd = torch.where(V.double().isfinite(), V.double(), torch.zeros((), dtype=torch.float64, device="cuda"))
     for b in range(2):
         _check(O[b][:, keep[b]], (ref[b] @ Vd[b])[:, keep[b]], dtype)
+
+
+# An infinity in one element of a key is a score of its sign times that of the head's value there: -inf has weight 0, +inf makes the head a NaN.
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("G,H,D", [(8, 100, 64), (8, 9, 64), (4, 70000, 64), (20, 300, 128)])
+@pytest.mark.parametrize("scale,qk_norm", [(0.125, False), (0.3, False), (-0.5, True)])
+def test_attention_infinities_of_k(dtype, G, H, D, scale, qk_norm):
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(48)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen).to(DTYPES[dtype])
+    Q, K, V = rand(2, G, D), rand(2, H, D), rand(2, H, D)
+    K[0, 5, 7], K[0, H - 1, 9], K[1, 3, 0] = float("inf"), -float("inf"), -float("inf")
+    Q[0, 0, 7], Q[0, 0, 9], Q[0, 1, 7], Q[0, 1, 9] = -1.0, 0.5, 1.0, -0.5
+    O = torch.empty_like(Q)
+    P.prism_gqa_decode_attention(Q, K, V, O, scale=scale, qk_norm=qk_norm)
+    Qd = Q.double()
+    if qk_norm:
+        Qd = Qd * torch.rsqrt(Qd.square().mean(-1, keepdim=True) + 1e-6)
+    ref = torch.softmax(torch.bmm(Qd, K.double().transpose(1, 2).contiguous()) * scale, -1) @ V.double()
+    assert torch.equal(O.isnan(), ref.isnan()) and 0 < int(ref.isnan().sum()) < ref.numel()
+    _check(O.nan_to_num(), ref.nan_to_num(), dtype)
+
+
+def test_attention_scores_that_only_the_factor_keeps_finite():
+    """bf16 Q and K whose products pass fp32's limit by themselves, and do not with the factor."""
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(49)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    Q, K, V = (rand(2, 8, 64) * 1e25).bfloat16(), (rand(2, 300, 64) * 1e15).bfloat16(), rand(2, 300, 64).bfloat16()
+    O = torch.empty_like(Q)
+    P.prism_gqa_decode_attention(Q, K, V, O, scale=3e-41)
+    # (the scale is a fp32 number with few bits: the one that the call sees)
+    s = float(torch.tensor(3e-41, dtype=torch.float32))
+    _check(O, torch.softmax(torch.bmm(Q.double(), K.double().transpose(1, 2).contiguous()) * s, -1) @ V.double(), "bf16")

@@ -2,6 +2,7 @@
 // widened to fp32 on load and rounded once, on the store of a result.
 #pragma once
 #include "device_utils.h"
+#include "prism_internal.h"
 
 namespace prism {
 
@@ -103,6 +104,70 @@ template <typename E, int V> __device__ __forceinline__ u32x4 column_operand(con
         }
     }
     return b;
+}
+
+// 16 rows x 16 C columns of a product call by one wavefront, with the fp32 matrix instructions over the whole of K: for wavefronts that met a sum
+// in parts that is not finite.  Few registers and little code, so that a kernel that hardly ever gets here carries neither; the price
+// is bounded by the latency of its loads, about a microsecond for every 16 K values.
+// m0: first row; column(p), p < 16 C: the column, -1 if it has none; stored(r, p): whether row m0 + r, column(p) is this wavefront's;
+// row_scale(r): 1/rms of row m0 + r.
+template <typename S, bool GATED, int C, typename Column, typename Stored, typename RowScale>
+__device__ __forceinline__ void products_in_f32(const typename S::elem* __restrict__ X, const typename S::elem* __restrict__ g,
+                                                const typename S::elem* __restrict__ W1, const typename S::elem* __restrict__ W2,
+                                                typename S::elem* __restrict__ Y, int M, int K, int N, int m0, int flags, Column column,
+                                                Stored stored, RowScale row_scale) {
+    typedef typename S::elem E;
+    constexpr int G = GATED ? 2 : 1;
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+    const bool gain = (flags & kFlagGain) != 0;
+    const E* x_lane = X + (size_t)min(m0 + c, M - 1) * K;
+    f32x4 acc[G][C];
+#pragma unroll
+    for (int m = 0; m < G; ++m)
+#pragma unroll
+        for (int j = 0; j < C; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+    for (int k0 = 0; k0 < K; k0 += 16) {
+        float a[4], w[G][C][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // lane q: K values 4 q .. of the sixteen; past the end zeros in both operands
+            const int k = min(k0 + 4 * q + i, K - 1);
+            const bool ok = k0 + 4 * q + i < K;
+            const float x = S::widen(x_lane[k]) * (gain ? S::widen(g[k]) : 1.f);
+            a[i] = ok ? x : 0.f;
+#pragma unroll
+            for (int m = 0; m < G; ++m)
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    const float v = S::widen((m == 0 ? W1 : W2)[(size_t)k * N + max(column(16 * j + c), 0)]);
+                    w[m][j][i] = ok ? v : 0.f;
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int m = 0; m < G; ++m)
+#pragma unroll
+                for (int j = 0; j < C; ++j) acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], w[m][j][i], acc[m][j], 0, 0, 0);
+    }
+    wait_stores_acknowledged();  // (what is stored now comes last)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 4 * q + e;
+        if (m >= M) continue;
+        const float rinv = row_scale(4 * q + e);
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int n = column(16 * j + c);
+            if (n < 0 || !stored(4 * q + e, 16 * j + c)) continue;
+            float y = acc[0][j][e] * rinv;
+            if (GATED) {
+                const float s = y;
+                y = ((flags & kFlagSilu) ? s / (1.0f + expf(-s)) : s) * (acc[G - 1][j][e] * rinv);
+            }
+            Y[(size_t)m * N + n] = S::narrow(y);
+        }
+    }
 }
 
 }  // namespace prism

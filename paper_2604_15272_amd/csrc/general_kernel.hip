@@ -24,6 +24,8 @@
 // 16-bit storage in parts against the fp32 instructions, whose products took 27 us of it: bf16 8 x 4096 x 32003 54.9 -> 43.5 us, gated bf16 8 x 4096 x 14331
 // 60.0 -> 48.8, f16 8 x 4096 x 32003 54.2 -> 48.6, bf16 40 x 4193 x 8041 51.8 -> 39.0, 169 x 500 x 3001 15.7 -> 12.7.  (fp32 storage would
 // need six products of three parts each, with w split anew for every 16 rows: no gain.)
+// Values that have no parts (infinities, NaNs, x * g past the format's range) make sums that are not finite; a wavefront that met one works its
+// outputs out once more with the fp32 instructions, at a bounded price (a NaN in the gain: bf16 8 x 4096 x 32003 40 -> 940 us).
 //
 // What bounds it: 16 rows of 16-bit storage: streaming W (262 MB at 6.0 TB/s); more rows: the operands' way from the caches; fp32
 // storage: the fp32 matrix rate, 256 operations per clock and compute unit (157 TFLOP/s).
@@ -222,6 +224,18 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
         ss[r] += __shfl_xor(ss[r], 32, 64);
         if (q == 0) ss_red[wave * (16 * RG) + 16 * r + c] = ss[r];
     }
+    bool bad = false;  // 16-bit storage: this thread met a sum that is not finite
+    // Column of place p in the tile; none past the right edge, and where a group of VW columns has been moved in from it, its first ones are the
+    // group's before it.
+    auto column = [&](int p) __attribute__((always_inline)) {
+        const int first = p / VW * VW, n = n0 + min(first, N - VW - n0) + p % VW;
+        return first >= N - n0 || n < n0 + first ? -1 : n;
+    };
+    auto row_scale = [&](int r, int row) __attribute__((always_inline)) {
+        float tot = 0.f;
+        for (int w = 0; w < nw; ++w) tot += ss_red[w * (16 * RG) + 16 * r + row];
+        return (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
+    };
     // Across wavefronts, one row group at a time.  Element e of accumulator tile j in lane (q, c) is row 4 q + e,
     // column j of the lane's VW.
 #pragma unroll
@@ -240,33 +254,37 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
         __syncthreads();
         for (int o = tid; o < 16 * TN; o += blockDim.x) {
             const int row = o / TN, col = o % TN;
-            const int m = m0 + 16 * r + row;
-            const int first = col / VW * VW;  // the column group as laid out, before the shift at the right edge
-            if (m >= M || first >= N - n0) continue;
-            const int n = n0 + min(first, N - VW - n0) + col % VW;
+            const int m = m0 + 16 * r + row, n = column(col);
+            if (m >= M || n < 0) continue;
             float v = 0.f, u = 0.f, tot = 0.f;
             for (int w = 0; w < nw; ++w) {
                 v += red[(w * 16 + row) * TN + col];
                 if (GATED) u += red[((nw + w) * 16 + row) * TN + col];
                 tot += ss_red[w * (16 * RG) + 16 * r + row];
             }
-            // 16-bit storage: a value without parts; the sum is worked out once more from the operands.
-            if (PARTS && !__builtin_isfinite(GATED ? fabsf(v) + fabsf(u) : v)) {
-                v = u = 0.f;
-#pragma clang loop unroll(disable)
-                for (int k = 0; k < K; ++k) {
-                    const float x = S::widen(X[(size_t)m * K + k]) * (gain ? S::widen(g[k]) : 1.f);
-                    v = fmaf(x, S::widen(W1[(size_t)k * N + n]), v);
-                    if (GATED) u = fmaf(x, S::widen(W2[(size_t)k * N + n]), u);
-                }
-            }
             const float rinv = (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
+            // (A row whose 1/rms is a NaN is one anyway.)
+            if (PARTS && !__builtin_isfinite(GATED ? fabsf(v) + fabsf(u) : v) && rinv == rinv) bad = true;
             float y = v * rinv;
             if (GATED) {
                 const float a = y;
                 y = ((flags & kFlagSilu) ? a / (1.0f + expf(-a)) : a) * (u * rinv);
             }
             Y[(size_t)m * N + n] = S::narrow(y);
+        }
+    }
+    if constexpr (PARTS) {
+        // Values past the format's range and infinities have no parts: a wavefront that met one works its outputs out once more in fp32.
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
+            constexpr int C = VW < 2 ? VW : 2;  // (an output's wavefront is that of its place in the tile, 64 at a time)
+#pragma clang loop unroll(disable)
+            for (int t = 0; t < RG * (VW / C); ++t) {
+                const int r = t / (VW / C), p0 = t % (VW / C) * (16 * C);
+                if (TN == 128 && nw % 2 == 0 && ((p0 / 64 ^ wave) & 1) != 0) continue;  // none of its own
+                products_in_f32<S, GATED, C>(
+                    X, g, W1, W2, Y, M, K, N, m0 + 16 * r, flags, [&](int p) { return column(p0 + p); },
+                    [&](int row, int p) { return (row * TN + p0 + p) / 64 % nw == wave; }, [&](int row) { return row_scale(r, row); });
+            }
         }
     }
 }

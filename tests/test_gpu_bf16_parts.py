@@ -191,3 +191,82 @@ def test_attention_scores_that_only_the_factor_keeps_finite():
     # (the scale is a fp32 number with few bits: the one that the call sees)
     s = float(torch.tensor(3e-41, dtype=torch.float32))
     _check(O, torch.softmax(torch.bmm(Q.double(), K.double().transpose(1, 2).contiguous()) * s, -1) @ V.double(), "bf16")
+
+
+# Products whose sums are not finite in parts: infinities and NaNs in W, an infinity in X (no normalisation: it stays one), values that only round to
+# infinity; in the first and last columns, where a group of columns is moved in from the right edge.
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (20, 301, 131), (40, 700, 1001), (15, 333, 4099), (200, 161, 515), (1999, 290, 2047), (1023, 501, 2046),
+                                   (1999, 60, 1023), (70, 17, 643)])
+@pytest.mark.parametrize("gated", [False, True])
+def test_sums_that_are_not_finite(dtype, M, K, N, gated):
+    import paper_2604_15272_amd as P
+    inf = float("inf")
+    gen = torch.Generator(device="cuda").manual_seed(50)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    X, W, W2 = rand(M, K), rand(K, N) * K ** -0.5, rand(K, N) * K ** -0.5
+    W[2, 0], W[3, N - 1], W[4, N - 2], W2[5, N // 2] = inf, -inf, float("nan"), inf
+    X, W, W2 = X.to(DTYPES[dtype]), W.to(DTYPES[dtype]), W2.to(DTYPES[dtype])
+    ones = torch.ones(K, device="cuda", dtype=DTYPES[dtype])
+    Y = torch.empty((M, N), dtype=DTYPES[dtype], device="cuda")
+
+    def check(ref):
+        assert torch.equal(Y.isnan(), ref.isnan()) and torch.equal(Y.isposinf(), ref.isposinf()) and torch.equal(Y.isneginf(), ref.isneginf())
+        keep = ref.isfinite()
+        _check(torch.where(keep, Y, 0), torch.where(keep, ref, 0), dtype)
+
+    Xd = X.double()
+    Xn = Xd * torch.rsqrt(Xd.square().mean(-1, keepdim=True) + 1e-6)
+    if gated:
+        P.prism_rmsnorm_glu(X, ones, W, W2, Y, eps=1e-6)
+        check((Xn @ W.double()) * (Xn @ W2.double()))
+        X[M - 1, 7] = inf
+        P.prism_swiglu(X, W, W2, Y)
+        Xd = X.double()
+        check(torch.nn.functional.silu(Xd @ W.double()) * (Xd @ W2.double()))
+    else:
+        P.prism_rmsnorm_matmul(X, ones, W, Y, eps=1e-6)
+        check(Xn @ W.double())
+
+
+# A NaN that reaches every output: a second pass at most, not a serial loop for each of them (tens of milliseconds here).
+@pytest.mark.parametrize("dtype,M,K,N", [("bf16", 8, 4096, 32003), ("f32", 1000, 4096, 2000), ("f16", 500, 4001, 2001)])
+def test_a_nan_in_the_gain_takes_bounded_time(dtype, M, K, N):
+    import paper_2604_15272_amd as P
+    X, g, W = (torch.ones(s, device="cuda", dtype=DTYPES[dtype]) for s in ((M, K), (K,), (K, N)))
+    Y = torch.empty((M, N), dtype=DTYPES[dtype], device="cuda")
+    times = []
+    for value in (1.0, float("nan")):
+        g[K // 2] = value
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        P.prism_rmsnorm_matmul(X, g, W, Y)
+        e[0].record()
+        for _ in range(5):
+            P.prism_rmsnorm_matmul(X, g, W, Y)
+        e[1].record()
+        torch.cuda.synchronize()
+        times.append(e[0].elapsed_time(e[1]) / 5)
+    print(f"{dtype} {M} x {K} x {N}: {times[0] * 1e3:.1f} us, with a NaN {times[1] * 1e3:.1f} us")
+    assert bool(Y.isnan().all()) and times[1] < 25 * times[0], times
+
+
+# Rows of NaNs are NaNs whatever their products: nothing is gone through again for them.
+@pytest.mark.parametrize("dtype,M,K,N", [("bf16", 8, 4096, 32003), ("f32", 1000, 4096, 2000)])
+def test_rows_of_nans_take_no_longer(dtype, M, K, N):
+    import paper_2604_15272_amd as P
+    X, g, W = (torch.ones(s, device="cuda", dtype=DTYPES[dtype]) for s in ((M, K), (K,), (K, N)))
+    Y = torch.empty((M, N), dtype=DTYPES[dtype], device="cuda")
+    times = []
+    for value in (1.0, float("nan")):
+        X[2, K // 2] = value
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        for _ in range(20):
+            P.prism_rmsnorm_matmul(X, g, W, Y)
+        e[0].record()
+        for _ in range(20):
+            P.prism_rmsnorm_matmul(X, g, W, Y)
+        e[1].record()
+        torch.cuda.synchronize()
+        times.append(e[0].elapsed_time(e[1]) / 20)
+    keep = torch.arange(M, device="cuda") != 2
+    assert bool(Y[2].isnan().all()) and bool(Y[keep].isfinite().all()) and times[1] < 2 * times[0], times

@@ -49,12 +49,15 @@ template <typename E> struct Piece<E, 1> {
 // 16-bit storage: products of 32-bit operands with stored values on the 16-bit matrix cores.  The operand goes in as P parts of
 // the storage format, the value rounded to it, what that leaves rounded again, and so on; the stored values are taken as they are.
 //   bf16: two parts carry a product of two stored values (16 significant bits) without loss, three any fp32 value.
-//   f16: two parts carry such a product (22 bits) without loss and a fp32 value to 2^-23; the second is 2^11 times as large as it
-//   should be, so that it does not run out of exponents before the first does, and has accumulators of its own.
+//   f16: two parts carry such a product (22 bits) without loss and a fp32 value to 2^-23, where it is 2^-14 or more; the second is 2^11 times as
+//   large as it should be, so that it does not run out of exponents before the first does, and has accumulators of its own.  Below 2^-14 the
+//   error is 2^-36.  Weights of a softmax, at most 1 and relative to each other, are therefore taken kWeightScale times as large, their
+//   sums too: 2^-23 of a weight down to 2^-29 of the largest, 2^-51 of the largest below.
 // Infinities, NaNs and what rounds to an infinity have no parts: the sum is not finite then.
 template <typename S> struct PartProduct;
 template <> struct PartProduct<StoreBf16> {
     static constexpr int kProductParts = 2, kFloatParts = 3, kAccumulators = 1;
+    static constexpr float kWeightScale = 1.f;
     template <int P> static __device__ __forceinline__ void split8(const float (&value)[8], u32x4 (&part)[P]) {
         float v[8];
 #pragma unroll
@@ -76,6 +79,8 @@ template <> struct PartProduct<StoreBf16> {
 };
 template <> struct PartProduct<StoreF16> {
     static constexpr int kProductParts = 2, kFloatParts = 2, kAccumulators = 2;
+    static constexpr float kWeightScale = 32768.f;
+    static constexpr float kLogWeight = 10.375f;  // the same by the exponent (e^10.375 = 32048), in few bits: differences from f16 values are exact
     template <int P> static __device__ __forceinline__ void split8(const float (&v)[8], u32x4 (&part)[P]) {
         static_assert(P == 2, "two parts");
 #pragma unroll

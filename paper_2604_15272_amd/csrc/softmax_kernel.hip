@@ -224,8 +224,8 @@ hipError_t launch_softmax_rows_16bit(const SoftmaxCall& c, bool f16) {
 // The frame of the fp32 product kernel (general_kernel.hip): RG groups of 16 rows and 16 * VW columns per workgroup, the
 // wavefronts take 32-deep K-blocks round-robin, lane (q, c) holds eight consecutive K values of row c and the same eight rows
 // of W at its VW columns.  Products: fp32 storage on the matrix cores in fp32, 16-bit storage on the 16-bit ones, the weight as parts (three of
-// bf16 carry it whole, two of f16 to 2^-23, less than the exponential's own error; PartProduct in any_shape.h).  The softmax rides in the operand: a running maximum per
-// row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
+// bf16 carry it whole, two of f16 to 2^-23 from 2^-29 of the largest weight on and to 2^-51 of the largest below; PartProduct in any_shape.h).
+// The softmax rides in the operand: a running maximum per row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
 // beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
 // The kernel this replaces (8 rows x 256 columns, one thread per column, two passes over X) was bound by its serial loads:
 // fp32 1624 x 3008 x 352 794 us, now 75 to 81 us.
@@ -264,6 +264,8 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
 
     constexpr bool PARTS = sizeof(E) == 2;
     constexpr int NA = std::is_same<S, StoreF16>::value ? 2 : 1;
+    // Weights in f16 parts are relative to exp(BELOW) of the largest (PartProduct): all of them, and so their sums.
+    constexpr float BELOW = std::is_same<S, StoreF16>::value ? PartProduct<StoreF16>::kLogWeight : 0.f;
     f32x4 acc[RG][VW][NA];
     float m_run[RG], l_run[RG];
 #pragma unroll
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
             for (int i = 1; i < XV; ++i) cm = fmaxf(cm, S::widen(b.x[r].at(i)));
             cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
             cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
-            const float m_new = fmaxf(m_run[r], cm);
+            const float m_new = fmaxf(m_run[r], cm - BELOW);
             if (__builtin_amdgcn_ballot_w64(m_new != m_run[r]) != 0) {
                 // Element e of an accumulator in lane (q, c) belongs to row 4 q + e, whose factor lives in the lanes of that
                 // row.  A row that has seen nothing yet keeps the factor 1.

@@ -301,3 +301,42 @@ def test_attention_a_nan_or_infinities_in_v_take_bounded_time(dtype, B, G, H, D)
     ref = w @ V.double()
     assert torch.equal(O.isnan(), ref.isnan()) and torch.equal(O.isposinf(), ref.isposinf()) and torch.equal(O.isneginf(), ref.isneginf())
     assert times[1] < 25 * times[0], times
+
+
+# The largest weight meets zeros of W or V, what is left are small weights: their own error counts.  f16 weights have 2^-22 of themselves (two parts, the
+# exponential's own rounding) from 2^-29 of the largest on, and 2^-51 of the largest below.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,K,N", [(9, 16383, 67), (3, 501, 131), (300, 161, 131), (700, 1001, 1283)])
+def test_softmax_of_small_weights(dtype, M, K, N):
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(52)
+    X = -torch.linspace(5.0, 27.0, M, device="cuda")[:, None].expand(M, K).contiguous()
+    W = torch.empty(K, N, device="cuda").uniform_(2e4, 6e4, generator=gen)
+    X[:, 3], W[3] = 0.0, 0.0
+    X, W = X.to(DTYPES[dtype]), W.to(DTYPES[dtype])
+    Y = torch.empty((M, N), dtype=DTYPES[dtype], device="cuda")
+    P.prism_softmax_matmul(X, W, Y)
+    w = torch.softmax(X.double(), -1)
+    ref = w @ W.double()
+    bits = 8 if dtype == "bf16" else 11
+    bound = ref * 2.0 ** -bits + (w * 2.0 ** -21 + (2.0 ** -51 if dtype == "f16" else 0.0)) @ W.double() + 2.0 ** -25
+    assert bool(((Y.double() - ref).abs() <= bound).all()), float(((Y.double() - ref).abs() / bound).max())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,G,H,D", [(2, 8, 16000, 64), (2, 20, 300, 128), (3, 4, 33, 64)])
+def test_attention_of_small_probabilities(dtype, B, G, H, D):
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(53)
+    Q, K = torch.zeros(B, G, D, device="cuda"), torch.zeros(B, H, D, device="cuda")
+    V = torch.empty(B, H, D, device="cuda").uniform_(2e4, 6e4, generator=gen)
+    Q[:, :, 0], K[:, :, 0] = torch.linspace(5.0, 27.0, G, device="cuda"), -1.0
+    K[:, H // 2], V[:, H // 2] = 0.0, 0.0
+    Q, K, V = (t.to(DTYPES[dtype]) for t in (Q, K, V))
+    O = torch.empty_like(Q)
+    P.prism_gqa_decode_attention(Q, K, V, O, scale=1.0)
+    w = torch.softmax(torch.bmm(Q.double(), K.double().transpose(1, 2).contiguous()), -1)
+    ref = w @ V.double()
+    bits = 8 if dtype == "bf16" else 11
+    bound = ref * 2.0 ** -bits + (w * 2.0 ** -21 + (2.0 ** -51 if dtype == "f16" else 0.0)) @ V.double() + 2.0 ** -25
+    assert bool(((O.double() - ref).abs() <= bound).all()), float(((O.double() - ref).abs() / bound).max())

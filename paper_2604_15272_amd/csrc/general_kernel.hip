@@ -1,6 +1,6 @@
 // Products for any M, K, N and every storage type, of 32-bit precision: fp32 storage on the matrix cores in fp32
 // (v_mfma_f32_16x16x4_f32), 16-bit storage on the 16-bit ones (v_mfma_f32_16x16x32), x * g as two parts that carry it without loss
-// and the stored w as it is (PartProduct in any_shape.h), so nothing is rounded between the inputs and the output.
+// (f16: products of 2^-14 or more; rows of smaller ones are worked out in fp32) and the stored w as it is (PartProduct in any_shape.h).
 //
 // A workgroup owns RG groups of 16 rows and 16 * VW columns; its wavefronts take the K-blocks (4 * XV deep, XV = the
 // values of 16 bytes) round-robin and meet in LDS after the loop.  The order of K inside a block is free as long as
@@ -90,10 +90,13 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     constexpr bool PARTS = general_in_parts<S, GATED, VW>();
     constexpr int NA = PARTS && std::is_same<S, StoreF16>::value ? 2 : 1;
     f32x4 acc[G][RG][VW][NA];
+    constexpr bool F16_PARTS = PARTS && std::is_same<S, StoreF16>::value;
     float ss[RG];
+    u32 products[RG];  // f16 in parts: the bits of the first ones or-ed
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         ss[r] = 0.f;
+        products[r] = 0;
 #pragma unroll
         for (int m = 0; m < G; ++m)
 #pragma unroll
@@ -145,6 +148,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
                     v[i] = x * (gain ? S::widen(b.g.at(i)) : 1.f);
                 }
                 PP::template split8<P>(v, a[r]);
+                if (F16_PARTS) products[r] |= a[r][0][0] | a[r][0][1] | a[r][0][2] | a[r][0][3];
             }
 #pragma unroll
             for (int m = 0; m < G; ++m)
@@ -189,12 +193,14 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     // (fp32 64 x 4096 x 4096 30.2 -> 27.0 us without; three blocks: the same, bf16 8 x 4096 x 32003 8 % slower).
     // In parts, one block at a time: in half the registers (and half the code, of which a short call runs little) more wavefronts share a SIMD: gated
     // bf16 13 x 256 x 1920 4.5 -> 3.9 us, bf16 8 x 512 x 1024 4.6 -> 3.9, 8 x 4096 x 32003 45.3 -> 43.5, gated 8 x 4096 x 14331 51.6 -> 48.8; 27 x 704
-    // x 2880 7.0 -> 7.2.  (fp32 39 x 5568 x 960 would take 76 us instead of 22.)
+    // x 2880 7.0 -> 7.2.  f16 and wide tiles: all loads of a block before its products, which the compiler else mixes (f16 8 x 4096 x 32003 50.9 us mixed, 45.2
+    // so; gated 8 x 4096 x 14331 56.0 / 50.6; narrow tiles lose 2 %).  (fp32 39 x 5568 x 960 would take 76 us instead of 22.)
     const int nfull = K / KB;
     if constexpr (PARTS) {
         for (int kb = wave; kb < nfull; kb += nw) {
             Blk b;
             load(b, kb);
+            if (F16_PARTS && VW >= 4) __builtin_amdgcn_sched_barrier(0);
             multiply(b);
         }
     } else if (wave < nfull) {
@@ -218,6 +224,22 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
         multiply(tail);
     }
 
+    if constexpr (F16_PARTS) {
+        // Rows of products too small for their parts: their sums are made NaNs, which has the outputs worked out in fp32 below.  (Without a gain the first
+        // part is x itself.)
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(gain && small_products(products[r], ss[r]));
+            if (__builtin_expect(lanes != 0, 0)) {
+                const u32 both = (u32)lanes | (u32)(lanes >> 32), rows = both | both >> 16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (rows >> (4 * q + e) & 1)
+#pragma unroll
+                        for (int j = 0; j < VW; ++j) acc[0][r][j][0][e] = __builtin_nanf("");
+            }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         ss[r] += __shfl_xor(ss[r], 16, 64);

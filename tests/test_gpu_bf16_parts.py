@@ -340,3 +340,28 @@ def test_attention_of_small_probabilities(dtype, B, G, H, D):
     bits = 8 if dtype == "bf16" else 11
     bound = ref * 2.0 ** -bits + (w * 2.0 ** -21 + (2.0 ** -51 if dtype == "f16" else 0.0)) @ V.double() + 2.0 ** -25
     assert bool(((O.double() - ref).abs() <= bound).all()), float(((O.double() - ref).abs() / bound).max())
+
+
+# f16: rows and gains whose products leave the range in which two parts carry them, and rows of zeros; relative to the products that an output sums, whose
+# own roundings are those of fp32 (as in test_error_against_64_bits), and of the stored output.
+@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (20, 301, 131), (40, 700, 1001), (15, 333, 4099), (200, 161, 515), (1999, 290, 2047), (1023, 501, 2046), (1999, 60, 1023)])
+@pytest.mark.parametrize("gain", [1.0, 1e-4])
+def test_f16_products_of_small_values(M, K, N, gain):
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(54)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    X = (rand(M, K) * 10.0 ** torch.linspace(-7, 0, M, device="cuda")[:, None]).half()
+    g, W = ((rand(K).abs() + 0.5) * gain).half(), rand(K, N).half()
+    X[M // 2] = 0.0
+    # Outputs of a size that f16 stores to 2^-11: a power of two undoes the gain's.
+    W *= 2.0 ** -round(float(torch.log2(torch.tensor(gain))) + 0.5 * float(torch.log2(torch.tensor(float(K)))))
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    P.prism_rmsnorm_matmul(X, g, W, Y, eps=0.0)
+    keep = (X != 0).any(1)
+    Xd = X.double()[keep]
+    r = torch.rsqrt(Xd.square().mean(-1, keepdim=True))
+    Xd = Xd * g.double()
+    ref, size = (Xd @ W.double()) * r, (Xd.abs() @ W.double().abs()) * r
+    bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + size * (2.0 ** -23 + 2.0 ** -24 * 4 * K ** 0.5)
+    assert bool(((Y.double()[keep] - ref).abs() <= bound).all()), float(((Y.double()[keep] - ref).abs() / bound).max())
+    assert bool(Y[~keep].isnan().all()) and int(keep.sum()) >= M // 2

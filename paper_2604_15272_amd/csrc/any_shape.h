@@ -51,8 +51,8 @@ template <typename E> struct Piece<E, 1> {
 //   bf16: two parts carry a product of two stored values (16 significant bits) without loss, three any fp32 value.
 //   f16: two parts carry such a product (22 bits) without loss and a fp32 value to 2^-23, where it is 2^-14 or more; the second is 2^11 times as
 //   large as it should be, so that it does not run out of exponents before the first does, and has accumulators of its own.  Below 2^-14 the
-//   error is 2^-36, no more than the rounding of a fp32 sum that has products of 2^-11 among them; rows of x * g where some lane has none of that
-//   size (small_products) are worked out in fp32.  Weights of a softmax, at most 1 and relative to each other, are therefore taken kWeightScale times as large, their
+//   error is 2^-36, no more than the rounding of a fp32 sum that has products of 2^-11 among them; rows of x * g that have none of that size
+//   (small_products) are worked out in fp32.  Weights of a softmax, at most 1 and relative to each other, are therefore taken kWeightScale times as large, their
 //   sums too: 2^-23 of a weight down to 2^-29 of the largest, 2^-51 of the largest below.
 // Infinities, NaNs and what rounds to an infinity have no parts: the sum is not finite then.
 template <typename S> struct PartProduct;
@@ -95,9 +95,9 @@ template <> struct PartProduct<StoreF16> {
     static __device__ __forceinline__ float sum(const f32x4 (&acc)[2], int e) { return fmaf(acc[1][e], 1.f / 2048.f, acc[0][e]); }
 };
 
-// Whether the products of x and g whose first f16 parts were or-ed into both halves of `bits` are all below 2^-11, and the x's, whose squares add up to ss,
-// not all 0.  (2^-11 is where the upper three bits of the exponent are first set, so the or of them tells.)
-__device__ __forceinline__ bool small_products(u32 bits, float ss) { return (bits & 0x70007000u) == 0 && ss != 0.f; }
+// Whether the products of x and g whose first f16 parts were or-ed into both halves of `bits` are all below 2^-11.  (2^-11 is where the upper three
+// bits of the exponent are first set, so the or of them tells.)
+__device__ __forceinline__ bool small_products(u32 bits) { return (bits & 0x70007000u) == 0; }
 
 // Column j of eight rows of V columns each, as a matrix operand: eight K values.
 template <typename E, int V> __device__ __forceinline__ u32x4 column_operand(const Piece<E, V> (&w)[8], int j) {

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     f32x4 acc[G][RG][VW][NA];
     constexpr bool F16_PARTS = PARTS && std::is_same<S, StoreF16>::value;
     float ss[RG];
-    u32 products[RG];  // f16 in parts: the bits of the first ones or-ed
+    u32 products[RG];  // f16 in parts: the bits of the first ones or-ed; one K-block's lane can see a single value, so the whole row decides
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         ss[r] = 0.f;
@@ -224,26 +224,17 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
         multiply(tail);
     }
 
-    if constexpr (F16_PARTS) {
-        // Rows of products too small for their parts: their sums are made NaNs, which has the outputs worked out in fp32 below.  (Without a gain the first
-        // part is x itself.)
-#pragma unroll
-        for (int r = 0; r < RG; ++r) {
-            const uint64_t lanes = __builtin_amdgcn_ballot_w64(gain && small_products(products[r], ss[r]));
-            if (__builtin_expect(lanes != 0, 0)) {
-                const u32 both = (u32)lanes | (u32)(lanes >> 32), rows = both | both >> 16;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (rows >> (4 * q + e) & 1)
-#pragma unroll
-                        for (int j = 0; j < VW; ++j) acc[0][r][j][0][e] = __builtin_nanf("");
-            }
-        }
-    }
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         ss[r] += __shfl_xor(ss[r], 16, 64);
         ss[r] += __shfl_xor(ss[r], 32, 64);
+        if constexpr (F16_PARTS) {
+            // A row's products can be too small for their parts: a wavefront that saw only such ones says so by the sign.  (Without a gain the first
+            // part is x itself.)
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(gain && small_products(products[r]));
+            const u32 both = (u32)lanes & (u32)(lanes >> 32), rows = both & both >> 16;
+            if (rows >> c & 1) ss[r] = -ss[r];
+        }
         if (q == 0) ss_red[wave * (16 * RG) + 16 * r + c] = ss[r];
     }
     bool bad = false;  // 16-bit storage: this thread met a sum that is not finite
@@ -255,7 +246,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     };
     auto row_scale = [&](int r, int row) __attribute__((always_inline)) {
         float tot = 0.f;
-        for (int w = 0; w < nw; ++w) tot += ss_red[w * (16 * RG) + 16 * r + row];
+        for (int w = 0; w < nw; ++w) tot += fabsf(ss_red[w * (16 * RG) + 16 * r + row]);
         return (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
     };
     // Across wavefronts, one row group at a time.  Element e of accumulator tile j in lane (q, c) is row 4 q + e,
@@ -282,11 +273,17 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
             for (int w = 0; w < nw; ++w) {
                 v += red[(w * 16 + row) * TN + col];
                 if (GATED) u += red[((nw + w) * 16 + row) * TN + col];
-                tot += ss_red[w * (16 * RG) + 16 * r + row];
+                const float squares = ss_red[w * (16 * RG) + 16 * r + row];
+                tot += F16_PARTS ? fabsf(squares) : squares;
             }
             const float rinv = (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
             // (A row whose 1/rms is a NaN is one anyway.)
             if (PARTS && !__builtin_isfinite(GATED ? fabsf(v) + fabsf(u) : v) && rinv == rinv) bad = true;
+            if (F16_PARTS && gain) {
+                float seen = 0.f;  // above 0 if some wavefront saw a product that is not too small
+                for (int w = 0; w < nw; ++w) seen = fmaxf(seen, ss_red[w * (16 * RG) + 16 * r + row]);
+                bad = bad | ((seen == 0.f) & (tot > 0.f));
+            }
             float y = v * rinv;
             if (GATED) {
                 const float a = y;

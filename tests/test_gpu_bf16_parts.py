@@ -365,3 +365,32 @@ def test_f16_products_of_small_values(M, K, N, gain):
     bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + size * (2.0 ** -23 + 2.0 ** -24 * 4 * K ** 0.5)
     assert bool(((Y.double()[keep] - ref).abs() <= bound).all()), float(((Y.double()[keep] - ref).abs() / bound).max())
     assert bool(Y[~keep].isnan().all()) and int(keep.sum()) >= M // 2
+
+
+# ... but one lane's share of an ordinary row can be small (the end of a ragged K has it hold a single value): no second pass for that.
+@pytest.mark.parametrize("M,K,N,gated,lanes", [(124, 169, 2437, True, slice(168, 169)), (397, 209, 759, False, slice(208, 209)), (8, 265, 8001, False, slice(264, 265)),
+                                               (1999, 290, 2047, False, slice(20, 290, 32)), (1023, 501, 1023, True, slice(8, 501, 64))])
+def test_f16_small_values_beside_ordinary_ones_take_no_longer(M, K, N, gated, lanes):
+    import paper_2604_15272_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(55)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    X, g, W = rand(M, K).half(), torch.ones(K, device="cuda", dtype=torch.float16), (rand(K, N) * K ** -0.5).half()
+    X[X.abs() < 0.01] = 0.01
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    call = (lambda: P.prism_rmsnorm_glu(X, g, W, W, Y)) if gated else (lambda: P.prism_rmsnorm_matmul(X, g, W, Y))
+    times = []
+    for step in range(2):
+        if step == 1:
+            for i in range(4 if lanes.step else 1):   # the four neighbouring values of a thread
+                X[:, lanes.start + i::lanes.step or K] = 1e-5
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        for _ in range(20):
+            call()
+        e[0].record()
+        for _ in range(20):
+            call()
+        e[1].record()
+        torch.cuda.synchronize()
+        times.append(e[0].elapsed_time(e[1]) / 20)
+    print(f"f16 {M} x {K} x {N}: {times[0] * 1e3:.1f} us, then {times[1] * 1e3:.1f} us")
+    assert times[1] < 1.5 * times[0], times

@@ -64,9 +64,9 @@ typedef enum {
 /* Kernel families.  AUTO picks by shape; the others are for tests and tuning sweeps. */
 typedef enum {
     PRISM_PATH_AUTO = 0,
-    PRISM_PATH_SIMPLE = 1,  /* fp32 arithmetic throughout: any M, K, N; the only path for PRISM_F32 */
-    PRISM_PATH_DECODE = 2,  /* few rows: W streamed once, split-K over wavefronts and workgroups; shallow K: also the
-                               kernel of PRISM_PATH_SIMPLE, unsplit (which AUTO may choose for any 16-bit call of up to 512 rows) */
+    PRISM_PATH_SIMPLE = 1,  /* products of 32-bit precision: any M, K, N; the only path for PRISM_F32, and AUTO takes
+                               shallow 16-bit calls there too */
+    PRISM_PATH_DECODE = 2,  /* few rows: W streamed once, split-K over wavefronts and workgroups */
     PRISM_PATH_PREFILL = 3, /* many rows: LDS-tiled MFMA GEMM */
     PRISM_PATH_ROWS = 4,    /* prism_softmax_matmul only: the matrix-core kernels (variant 16: 16 rows of X over the
                                whole of K per workgroup; variant 32: 32 rows and one of up to 16 K-slices) */

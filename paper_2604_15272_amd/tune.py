@@ -157,11 +157,13 @@ def tune(op, M, K, N, dtype=B.PRISM_BF16, samples=12, seed=0, steps=None, instal
     B.prism_set_override(0, 0, 0)
     saved_entry_plan = B.prism_plan(op, M, K, N, dtype)  # what the library does today (table or heuristic)
     cands = candidates(op, M, K, N, dtype)
-    default = next((c for c in cands if c["plan"] == saved_entry_plan), None)
+    # (A plan that no assignment by name reproduces is timed as the library's own choice.)
+    default = next((c for c in cands if c["plan"] == saved_entry_plan),
+                   {"path": B.PRISM_PATH_AUTO, "split_k": 0, "variant": 0, "plan": saved_entry_plan})
     rng = random.Random(seed)
     rest = [c for c in cands if c is not default and c["path"] != B.PRISM_PATH_SIMPLE]
     rng.shuffle(rest)
-    chosen = ([default] if default is not None else []) + rest[:max(0, samples - (default is not None))]
+    chosen = [default] + rest[:max(0, samples - 1)]
 
     flops = 2.0 * M * K * N * nw
     if steps is None:
@@ -186,7 +188,7 @@ def tune(op, M, K, N, dtype=B.PRISM_BF16, samples=12, seed=0, steps=None, instal
     if not tried:
         raise RuntimeError("no admissible assignment could be timed")
     best = min(tried, key=lambda t: t["us"])
-    dflt = next((t for t in tried if default is not None and t["plan"] == default["plan"]), None)
+    dflt = next((t for t in tried if t["plan"] == default["plan"]), None)
     if install:
         B.prism_plan_table_set(op, M, K, N, dtype, best["path"], best["split_k"], best["variant"])
         B.ensure_workspace(B.prism_workspace_bytes(op, M, K, N, dtype))

@@ -784,7 +784,7 @@ def _softmax_case(P, dtype, M, K, N, seed, path=0, x_std=3.0, expect_path=None, 
 @pytest.mark.parametrize("M,K,N", [(1, 8, 8), (16, 512, 128), (33, 1000, 264), (100, 4096, 128), (7, 72, 16),
                                    (257, 2056, 136), (64, 8200, 128)])
 def test_softmax_matmul_rows_kernel(P, dtype, M, K, N):
-    _softmax_case(P, dtype, M, K, N, seed=1000 + M + K, expect_path=P.PRISM_PATH_ROWS)
+    _softmax_case(P, dtype, M, K, N, seed=1000 + M + K, path=P.PRISM_PATH_ROWS)
 
 
 @pytest.mark.parametrize("rows", [16, 32])

@@ -81,6 +81,21 @@ def test_products_and_softmax(P, op, dtype, M, K, N):
     _compare(P.prism_plan(op, M, K, N, code), _recorded(call))
 
 
+# Kernels by name, of calls that the dispatcher gives to another one.
+@pytest.mark.parametrize("path,split,variant,op,dtype,M,K,N", [
+    (2, 0, 0, 1, "f16", 8, 1024, 4096), (2, 0, 0, 1, "bf16", 40, 512, 1024), (2, 0, 108, 1, "bf16", 8, 512, 1024), (2, 3, 64, 0, "f16", 100, 512, 520),
+    (2, 0, 0, 0, "bf16", 8, 512, 1024), (3, 0, 0, 1, "f16", 192, 512, 384), (1, 0, 0, 0, "bf16", 16, 4096, 4096), (1, 0, 0, 1, "f16", 2048, 512, 1024),
+    (4, 0, 16, 2, "f16", 48, 1024, 128), (4, 2, 32, 2, "bf16", 48, 1024, 128), (1, 0, 0, 2, "f16", 4096, 512, 128)])
+def test_kernels_by_name(P, path, split, variant, op, dtype, M, K, N):
+    P.prism_set_override(path, split, variant)
+    try:
+        code = {"bf16": P.PRISM_BF16, "f16": P.PRISM_F16}[dtype]
+        assert P.prism_plan(op, M, K, N, code)["path"] == path
+        test_products_and_softmax(P, op, dtype, M, K, N)
+    finally:
+        P.prism_set_override(0, 0, 0)
+
+
 @pytest.mark.parametrize("dtype,B,G,H,D", [("f16", 2, 8, 2048, 128), ("bf16", 3, 5, 100, 128), ("f32", 2, 8, 2048, 128),
                                            ("f16", 2, 8, 2000, 64), ("bf16", 3, 33, 700, 128), ("f32", 3, 33, 20, 64),
                                            ("f32", 2, 7, 300, 80)])

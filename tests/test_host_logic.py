@@ -606,6 +606,26 @@ def test_tuner_enumerates_admissible_assignments(P):
     assert P.prism_plan(0, 16, 2048, 1024, P.PRISM_BF16)["path"] == P.PRISM_PATH_DECODE  # override is reset
 
 
+def test_the_heuristics_plan_is_among_the_tuners_candidates(P):
+    """A plan names the kernel that runs, so that asking for it by name gives the same plan."""
+    import random
+    from paper_2604_15272_amd import tune
+    bf16, f16, sm = P.PRISM_BF16, P.PRISM_F16, P.PRISM_OP_SOFTMAX_MATMUL
+    cases = [(1, 13, 256, 1920, bf16), (1, 8, 1024, 4096, f16), (0, 7, 896, 1792, bf16), (1, 27, 704, 2880, bf16), (0, 100, 512, 512, bf16),
+             (sm, 51, 256, 672, f16), (sm, 55, 640, 224, bf16), (sm, 16, 512, 128, f16), (sm, 4054, 352, 64, bf16), (0, 8, 256, 512, P.PRISM_F32)]
+    rng = random.Random(7)
+    for _ in range(60):
+        cases.append((rng.choice((0, 1, sm)), int(2 ** rng.uniform(0, 11)), 8 * int(2 ** rng.uniform(3, 9)), 8 * int(2 ** rng.uniform(0, 10)),
+                      rng.choice((bf16, f16))))
+    P.prism_diag_set_cu_count(256)
+    try:
+        for case in cases:
+            plan = P.prism_plan(*case)
+            assert plan in [c["plan"] for c in tune.candidates(*case)], (case, plan)
+    finally:
+        P.prism_diag_set_cu_count(0)
+
+
 def test_inputs_are_deterministic_and_bf16_exact():
     import numpy as np
     import prism_inputs as pi
@@ -726,11 +746,12 @@ def test_shallow_k_on_the_kernel_for_any_shape(P):
                                 (0, f16, 6, 320, 13056), (1, bf16, 167, 832, 128), (1, bf16, 34, 512, 1536), (2, f16, 51, 256, 672),
                                 (2, bf16, 55, 640, 224)):   # 4.5 / 8.2, 4.7 / 8.8, 5.0 / 9.3, 4.5 / 6.5, 4.5 / 6.4, 5.4 / 10.6, 5.8 / 10.3, 4.2 / 7.9, 5.1 / 8.3
             p = plan(op, dt, M, K, N)
-            assert p["workspace_bytes"] == 0 and p["split_k"] == 1 and p["tile_n"] in (16, 64, 128) and p["tile_m"] in (16, 32), p
+            assert p["path"] == P.PRISM_PATH_SIMPLE and p["workspace_bytes"] == 0 and p["split_k"] == 1, p
+            assert p["tile_n"] in (16, 64, 128) and p["tile_m"] in (16, 32), p
             assert (p["grid_x"], p["grid_y"]) == (-(-N // p["tile_n"]), -(-M // p["tile_m"])), p
-        for op, dt, M, K, N in ((1, f16, 12, 960, 6656), (1, f16, 2, 2368, 6912), (0, bf16, 16, 4096, 4096), (1, f16, 95, 192, 4160)):  # 14.9 / 11.2, 23 / 15.5, 18.7 / 10.7, 10.2 / 7.6
-            p = plan(op, dt, M, K, N)
-            assert not (p["tile_n"] == 128 and p["split_k"] == 1 and p["tile_m"] == 16 and p["grid_y"] > 1) and p["tile_n"] != 16, p
+        for op, dt, M, K, N in ((1, f16, 12, 960, 6656), (1, f16, 2, 2368, 6912), (0, bf16, 16, 4096, 4096), (1, f16, 95, 192, 4160)):
+            p = plan(op, dt, M, K, N)   # eight columns per lane 14.9, 23, 18.7, 10.2; 11.2, 15.5, 10.7, 7.6
+            assert (p["path"], p["tile_n"]) != (P.PRISM_PATH_SIMPLE, 128), p
         P.prism_set_stream_balance(0x0808, 0)
         try:
             assert plan(1, bf16, 13, 256, 1920)["tile_n"] != 16

@@ -737,7 +737,8 @@ def test_the_parity_cases_take_every_form_of_the_fp32_kernels(P):
 
 def test_shallow_k_on_the_kernel_for_any_shape(P):
     """16-bit calls of few rows and shallow K, products and softmax (us on an MI355X: this form / the kernels with K-slices or
-    tiles); no workspace where they take it.  A caller who balances the decode kernel's streams keeps that kernel."""
+    tiles); no workspace where they take it.  A caller who balances the decode kernel's streams keeps that kernel for the calls
+    that this changes."""
     P.prism_diag_set_cu_count(256)
     try:
         bf16, f16 = P.PRISM_BF16, P.PRISM_F16
@@ -752,9 +753,15 @@ def test_shallow_k_on_the_kernel_for_any_shape(P):
         for op, dt, M, K, N in ((1, f16, 12, 960, 6656), (1, f16, 2, 2368, 6912), (0, bf16, 16, 4096, 4096), (1, f16, 95, 192, 4160)):
             p = plan(op, dt, M, K, N)   # eight columns per lane 14.9, 23, 18.7, 10.2; 11.2, 15.5, 10.7, 7.6
             assert (p["path"], p["tile_n"]) != (P.PRISM_PATH_SIMPLE, 128), p
+        # ... of those whose streams it changes (gated, at most 16 rows, a pitch that keeps tiles in their units), and no other
+        free = {c: plan(*c) for c in ((1, bf16, 13, 256, 1920), (0, bf16, 100, 512, 512), (0, f16, 8, 512, 1024), (1, f16, 31, 256, 2048))}
         P.prism_set_stream_balance(0x0808, 0)
         try:
-            assert plan(1, bf16, 13, 256, 1920)["tile_n"] != 16
+            for c, p in free.items():
+                assert p["path"] == P.PRISM_PATH_SIMPLE and plan(*c) == p, c
+            for c in ((1, f16, 8, 1024, 4096), (1, bf16, 3, 512, 7168)):
+                p = plan(*c)
+                assert p["path"] == P.PRISM_PATH_DECODE and p["tile_n"] == 64 and p["grid_x"] > c[4] // 64, p
         finally:
             P.prism_set_stream_balance(0, 0)
     finally:

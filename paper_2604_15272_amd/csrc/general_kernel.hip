@@ -45,12 +45,6 @@ template <typename E, int XV, int VW, int RG, int G> struct Block {
     Piece<E, VW> w[G][XV];
 };
 
-// 16-bit storage on the 16-bit matrix cores, in parts (PartProduct).  Two f16 matrices with eight columns per lane would need
-// 128 accumulators beside two blocks of 80 registers: that form stays in fp32.
-template <typename S, bool GATED, int VW> constexpr bool general_in_parts() {
-    return sizeof(typename S::elem) == 2 && !(std::is_same<S, StoreF16>::value && GATED && VW == 8);
-}
-
 }  // namespace
 
 // LDS: [G][waves][16][16 * VW] partial products of one row group, [waves][16 * RG] sums of squares.
@@ -87,7 +81,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     for (int r = 0; r < RG; ++r) x_lane[r] = X + (size_t)min(m0 + 16 * r + c, M - 1) * K + XV * q;
     const E* g_lane = (gain ? g : X) + XV * q;  // (without a gain the load is of no use, but it keeps the loop free of branches)
 
-    constexpr bool PARTS = general_in_parts<S, GATED, VW>();
+    constexpr bool PARTS = sizeof(E) == 2;  // 16-bit storage on the 16-bit matrix cores, in parts (PartProduct)
     constexpr int NA = PARTS && std::is_same<S, StoreF16>::value ? 2 : 1;
     f32x4 acc[G][RG][VW][NA];
     constexpr bool F16_PARTS = PARTS && std::is_same<S, StoreF16>::value;
@@ -329,8 +323,8 @@ static hipError_t launch_general_form(const Call& c) {
     switch (c.form.row_groups * 10 + c.form.cols) {
         case 11: return launch_general_as<S, GATED, 1, 1>(c);
         case 14: return launch_general_as<S, GATED, 1, 4>(c);
-        case 18: if constexpr (!wide) return launch_general_as<S, GATED, 1, 8>(c); else break;
-        case 21: return launch_general_as<S, GATED, 2, 1>(c);
+        case 18: if constexpr (!wide && !(GATED && std::is_same<S, StoreF16>::value)) return launch_general_as<S, GATED, 1, 8>(c); else break;
+        case 21: if constexpr (wide || GATED) return launch_general_as<S, GATED, 2, 1>(c); else break;
         case 24: return launch_general_as<S, GATED, 2, 4>(c);
     }
     return hipErrorInvalidValue;

@@ -145,7 +145,7 @@ def test_attention_fp32_kernel_large_values_before_the_maximum(P, dtype, G, H, D
 
 # Every form of the fp32 kernels, the plan's as well as the result's.
 @pytest.mark.parametrize("dtype,gated,form,shape", [(dt, g, f, s) for dt in (pi.F32, pi.BF16, pi.F16) for g in (False, True)
-                                                    for f, s in fp32_forms.PRODUCTS[g, dt == pi.F32]])
+                                                    for f, s in fp32_forms.PRODUCTS[g, dt]])
 def test_every_form_of_the_fp32_products(P, dtype, gated, form, shape):
     plan = P.prism_plan(int(gated), *shape, DTYPE_CODE[dtype])
     assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
@@ -221,7 +221,8 @@ def test_any_shape_infinities_of_w_stay_in_their_column(P, gated, M, K, N):
                                               (1999, 37, 1023, True, (64, 64, 512)), (3001, 17, 1001, True, (128, 64, 512))])
 def test_shallow_k_forms(P, dtype, M, K, N, gated, form):
     plan = P.prism_plan(int(gated), M, K, N, DTYPE_CODE[dtype])
-    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or P.prism_diag_cu_count() != 256
+    # (fp32 beyond K = 64 goes by the estimates of a deep K)
+    assert (plan["tile_m"], plan["tile_n"], plan["block"]) == form or (dtype == pi.F32 and K > 64) or P.prism_diag_cu_count() != 256
     _case(P, dtype, M, K, N, gated, seed=290 + K, expect_path=P.PRISM_PATH_SIMPLE)
 
 

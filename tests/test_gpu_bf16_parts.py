@@ -394,3 +394,36 @@ def test_f16_small_values_beside_ordinary_ones_take_no_longer(M, K, N, gated, la
         times.append(e[0].elapsed_time(e[1]) / 20)
     print(f"f16 {M} x {K} x {N}: {times[0] * 1e3:.1f} us, then {times[1] * 1e3:.1f} us")
     assert times[1] < 1.5 * times[0], times
+
+
+# 16-bit calls of a shallow K as a default user's are dispatched: every form of the kernel for any shape that they take, rows and columns past a tile.
+# 0: one matrix, 1: two, 2: softmax.
+@pytest.mark.parametrize("op,dtype,M,K,N,form", [
+    (0, "bf16", 136, 96, 1800, (16, 16, 256)), (0, "f16", 1, 64, 24, (16, 16, 512)), (0, "bf16", 1, 64, 8264, (16, 64, 512)), (0, "f16", 34, 64, 8840, (16, 128, 512)),
+    (0, "f16", 17, 96, 8680, (32, 64, 512)), (0, "bf16", 18, 64, 9960, (32, 64, 512)), (0, "bf16", 8, 1024, 1024, (16, 16, 512)), (0, "f16", 512, 512, 40, (16, 16, 512)),
+    (1, "f16", 1, 64, 6168, (16, 16, 256)), (1, "f16", 8, 1024, 4096, (16, 16, 512)), (1, "f16", 35, 64, 9440, (16, 64, 256)), (1, "bf16", 1, 64, 8296, (16, 64, 512)),
+    (1, "bf16", 75, 64, 11656, (16, 128, 256)), (1, "bf16", 39, 64, 8408, (16, 128, 512)), (1, "f16", 21, 64, 8304, (32, 16, 256)), (1, "f16", 18, 64, 2352, (32, 16, 512)),
+    (1, "bf16", 69, 64, 10680, (32, 64, 256)), (1, "bf16", 18, 64, 8760, (32, 64, 512)), (2, "bf16", 1, 32, 8, (16, 16, 512)), (2, "f16", 51, 256, 672, (16, 16, 512)),
+    (2, "bf16", 1, 40, 4128, (16, 64, 512)), (2, "f16", 19, 32, 9528, (16, 128, 512)), (2, "bf16", 2296, 32, 136, (32, 64, 512)), (2, "f16", 2179, 40, 168, (32, 64, 512))])
+def test_shallow_16_bit_calls_as_dispatched(op, dtype, M, K, N, form):
+    import paper_2604_15272_amd as P
+    P.prism_set_override(0, 0, 0)
+    plan = P.prism_plan(op, M, K, N, _code(P, dtype))
+    assert (plan["path"] == P.PRISM_PATH_SIMPLE and (plan["tile_m"], plan["tile_n"], plan["block"]) == form) or P.prism_diag_cu_count() != 256, plan
+    gen = torch.Generator(device="cuda").manual_seed(61)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    X, g = (rand(M, K) * (3.0 if op == 2 else 1.0)).to(DTYPES[dtype]), (rand(K).abs() + 0.5).to(DTYPES[dtype])
+    W, W2 = ((rand(K, N) * (1.0 if op == 2 else K ** -0.5)).to(DTYPES[dtype]) for _ in range(2))
+    Y = torch.full((M, N), float("nan"), dtype=DTYPES[dtype], device="cuda")
+    Xd = X.double()
+    if op == 2:
+        P.prism_softmax_matmul(X, W, Y)
+        _check(Y, torch.softmax(Xd, -1) @ W.double(), dtype)
+        return
+    Xn = Xd * torch.rsqrt(Xd.square().mean(-1, keepdim=True) + 1e-6) * g.double()
+    if op == 1:
+        P.prism_rmsnorm_gated_mlp(X, g, W, W2, Y, eps=1e-6)
+        _check(Y, torch.nn.functional.silu(Xn @ W.double()) * (Xn @ W2.double()), dtype)
+    else:
+        P.prism_rmsnorm_matmul(X, g, W, Y, eps=1e-6)
+        _check(Y, Xn @ W.double(), dtype)

@@ -383,6 +383,7 @@ def test_decode_slow_tiles_first_changes_the_order_only(P, M, K, N, gated, units
             outs = []
             for u in (0, units):
                 P.prism_set_stream_balance(u, 0)
+                P.prism_set_override(P.PRISM_PATH_DECODE, 0, 0)
                 plan = P.prism_plan(int(gated), M, K, N, P.PRISM_BF16)
                 assert plan["path"] == P.PRISM_PATH_DECODE and plan["grid_x"] * plan["grid_y"] > P.prism_diag_cu_count(), plan
                 Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
@@ -392,6 +393,7 @@ def test_decode_slow_tiles_first_changes_the_order_only(P, M, K, N, gated, units
             assert torch.equal(outs[0].view(torch.uint16), outs[1].view(torch.uint16)), (units, shift)
             assert_parity(from_device(outs[1], pi.BF16), yhat, pi.BF16, f"slow tiles first, units {units:#x}, W at {2 * shift}")
     finally:
+        P.prism_set_override(0, 0, 0)
         P.prism_set_stream_balance(0x0808, 0)
 
 
@@ -538,11 +540,15 @@ def test_decode_rows_with_x_through_lds_every_split_and_row_count(P, split, rows
 @pytest.mark.parametrize("dtype,M,K,N", [(pi.BF16, 512, 4096, 1024), (pi.F16, 200, 4104, 520), (pi.BF16, 33, 2048, 136),
                                          (pi.F16, 500, 8192, 256)])
 def test_decode_rows_with_x_through_lds_as_dispatched(P, dtype, M, K, N):
-    """Long slices of one weight matrix: the dispatcher takes that loop by itself; with and without gain."""
-    plan = P.prism_plan(0, M, K, N, DTYPE_CODE[dtype])
-    assert plan["path"] == P.PRISM_PATH_DECODE and plan["tile_m"] in (32, 64), plan
-    _case(P, dtype, M, K, N, False, seed=475)
-    _variant_case(P, dtype, M, K, N, "plain_nogain", seed=476)
+    """Long slices of one weight matrix: the decode path takes that loop by itself; with and without gain."""
+    P.prism_set_override(P.PRISM_PATH_DECODE, 0, 0)
+    try:
+        plan = P.prism_plan(0, M, K, N, DTYPE_CODE[dtype])
+    finally:
+        P.prism_set_override(0, 0, 0)
+    assert plan["tile_m"] in (32, 64), plan
+    _case(P, dtype, M, K, N, False, seed=475, path=P.PRISM_PATH_DECODE)
+    _variant_case(P, dtype, M, K, N, "plain_nogain", seed=476, path=P.PRISM_PATH_DECODE)
 
 
 # Rows of W that are no multiple of 128 bytes, over 41 column tiles (five runs of neighbours and one left over) and 261.

@@ -41,7 +41,7 @@ def test_static_scratch_entry_point_two_calls_in_a_row_then_too_large():
     import paper_2604_15272_amd as P
     P.prism_set_override(0, 0, 0)
     _both(P, 16, 4096, 4096, 8101)     # benchmark configuration 2: eight K-slices, 2.3 MB of scratch
-    _both(P, 7, 1024, 1000, 8102)      # smaller, ragged: the array still holds the first call's partials
+    _both(P, 7, 2560, 1000, 8102)      # smaller, ragged: the array still holds the first call's partials
     _both(P, 16, 4096, 4096, 8103)
     # a call that needs more scratch than the array holds is refused, and nothing is launched
     M, K, N = 64, 8192, 8192

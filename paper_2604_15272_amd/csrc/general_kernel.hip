@@ -45,10 +45,17 @@ template <typename E, int XV, int VW, int RG, int G> struct Block {
     Piece<E, VW> w[G][XV];
 };
 
+// K from which 16 x 16 tiles of one 16-bit matrix request a block ahead.  There are few wavefronts then, and each walks ten blocks or more with nothing but the
+// others of its SIMD to hide the loads (us, ahead / one block at a time: f16 12 x 3501 x 41 13.1 / 15.0, 100 x 6001 x 500 23.0 / 25.7, bf16
+// 189 x 3501 x 83 14.8 / 16.0, 16 x 2601 x 1287 11.1 / 11.3; shorter and no better on average: f16 189 x 2049 x 83 11.4 / 10.1, 16 x 1801 x 1287 8.5 / 9.1,
+// bf16 100 x 601 x 500 5.2 / 5.0; two matrices: 0.82 of the time of two blocks with one, K 512 to 4096, 0.93 beyond).
+constexpr int kNarrowAheadK = 2560;
+
 }  // namespace
 
+// AHEAD: the next K-block is requested before the present one is multiplied (see the loop).
 // LDS: [G][waves][16][16 * VW] partial products of one row group, [waves][16 * RG] sums of squares.
-template <typename S, bool GATED, int RG, int VW>
+template <typename S, bool GATED, int RG, int VW, bool AHEAD>
 __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel(
     const typename S::elem* __restrict__ X, const typename S::elem* __restrict__ g,
     const typename S::elem* __restrict__ W1, const typename S::elem* __restrict__ W2, typename S::elem* __restrict__ Y,
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     // x 2880 7.0 -> 7.2.  f16 and wide tiles: all loads of a block before its products, which the compiler else mixes (f16 8 x 4096 x 32003 50.9 us mixed, 45.2
     // so; gated 8 x 4096 x 14331 56.0 / 50.6; narrow tiles lose 2 %).  (fp32 39 x 5568 x 960 would take 76 us instead of 22.)
     const int nfull = K / KB;
-    if constexpr (PARTS) {
+    if constexpr (!AHEAD) {
         for (int kb = wave; kb < nfull; kb += nw) {
             Blk b;
             load(b, kb);
@@ -302,14 +309,14 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     }
 }
 
-template <typename S, bool GATED, int RG, int VW>
+template <typename S, bool GATED, int RG, int VW, bool AHEAD = sizeof(typename S::elem) == 4>
 static hipError_t launch_general_as(const Call& c) {
     const int waves = c.form.waves;
     typedef typename S::elem E;
     const int tn = 16 * VW;
     dim3 grid((c.N + tn - 1) / tn, (c.M + 16 * RG - 1) / (16 * RG)), block(waves * 64);
     const size_t lds = ((size_t)(GATED ? 2 : 1) * waves * 16 * tn + (size_t)waves * 16 * RG) * sizeof(float);
-    auto kern = general_kernel<S, GATED, RG, VW>;
+    auto kern = general_kernel<S, GATED, RG, VW, AHEAD>;
     static std::atomic<uint64_t> opted{0};
     if (hipError_t e = allow_large_lds((const void*)kern, lds, opted); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, c.stream, (const E*)c.X, (const E*)c.g, (const E*)c.W1,
@@ -321,7 +328,11 @@ template <typename S, bool GATED>
 static hipError_t launch_general_form(const Call& c) {
     constexpr bool wide = sizeof(typename S::elem) == 4;
     switch (c.form.row_groups * 10 + c.form.cols) {
-        case 11: return launch_general_as<S, GATED, 1, 1>(c);
+        case 11:
+            if constexpr (!wide && !GATED) {
+                if (c.K >= kNarrowAheadK) return launch_general_as<S, GATED, 1, 1, true>(c);
+            }
+            return launch_general_as<S, GATED, 1, 1>(c);
         case 14: return launch_general_as<S, GATED, 1, 4>(c);
         case 18: if constexpr (!wide && !(GATED && std::is_same<S, StoreF16>::value)) return launch_general_as<S, GATED, 1, 8>(c); else break;
         case 21: if constexpr (wide || GATED) return launch_general_as<S, GATED, 2, 1>(c); else break;

@@ -86,7 +86,7 @@ def test_error_against_64_bits(M, K, N):
 # 16-bit storage: x * g beyond the format's range (and a third of it near the f16 limit), small rows whose second part would leave f16's
 # exponents unscaled, and a column of large weights; one case per form of the kernels.
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (40, 700, 1001), (15, 333, 4099), (18, 69, 4255), (132, 71, 3555), (200, 161, 515), (7600, 81, 33), (1999, 290, 2047), (1023, 501, 2046), (1999, 60, 1023)])
+@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (12, 2601, 41), (20, 4128, 35), (40, 700, 1001), (15, 333, 4099), (18, 69, 4255), (132, 71, 3555), (200, 161, 515), (7600, 81, 33), (1999, 290, 2047), (1023, 501, 2046), (1999, 60, 1023)])
 def test_16_bit_storage_at_the_ends_of_its_range(dtype, M, K, N):
     import paper_2604_15272_amd as P
     gen = torch.Generator(device="cuda").manual_seed(44)
@@ -344,7 +344,7 @@ def test_attention_of_small_probabilities(dtype, B, G, H, D):
 
 # f16: rows and gains whose products leave the range in which two parts carry them, and rows of zeros; relative to the products that an output sums, whose
 # own roundings are those of fp32 (as in test_error_against_64_bits), and of the stored output.
-@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (40, 700, 1001), (15, 333, 4099), (18, 69, 4255), (132, 71, 3555), (200, 161, 515), (7600, 81, 33), (1999, 290, 2047), (1023, 501, 2046), (1999, 60, 1023)])
+@pytest.mark.parametrize("M,K,N", [(5, 301, 131), (12, 2601, 41), (20, 4128, 35), (40, 700, 1001), (15, 333, 4099), (18, 69, 4255), (132, 71, 3555), (200, 161, 515), (7600, 81, 33), (1999, 290, 2047), (1023, 501, 2046), (1999, 60, 1023)])
 @pytest.mark.parametrize("gain", [1.0, 1e-4])
 def test_f16_products_of_small_values(M, K, N, gain):
     import paper_2604_15272_amd as P

@@ -400,10 +400,10 @@ def test_f16_small_values_beside_ordinary_ones_take_no_longer(M, K, N, gated, la
 # 0: one matrix, 1: two, 2: softmax.
 @pytest.mark.parametrize("op,dtype,M,K,N,form", [
     (0, "bf16", 136, 96, 1800, (16, 16, 256)), (0, "f16", 1, 64, 24, (16, 16, 512)), (0, "bf16", 1, 64, 8264, (16, 64, 512)), (0, "f16", 34, 64, 8840, (16, 128, 512)),
-    (0, "f16", 17, 96, 8680, (32, 64, 512)), (0, "bf16", 18, 64, 9960, (32, 64, 512)), (0, "bf16", 8, 1024, 1024, (16, 16, 512)), (0, "f16", 512, 512, 40, (16, 16, 512)),
+    (0, "f16", 454, 96, 1072, (32, 64, 512)), (0, "bf16", 81, 64, 5392, (32, 64, 512)), (0, "bf16", 8, 1024, 1024, (16, 16, 512)), (0, "f16", 512, 512, 40, (16, 16, 512)),
     (1, "f16", 1, 64, 6168, (16, 16, 256)), (1, "f16", 8, 1024, 4096, (16, 16, 512)), (1, "f16", 35, 64, 9440, (16, 64, 256)), (1, "bf16", 1, 64, 8296, (16, 64, 512)),
-    (1, "bf16", 75, 64, 11656, (16, 128, 256)), (1, "bf16", 39, 64, 8408, (16, 128, 512)), (1, "f16", 21, 64, 8304, (32, 16, 256)), (1, "f16", 18, 64, 2352, (32, 16, 512)),
-    (1, "bf16", 69, 64, 10680, (32, 64, 256)), (1, "bf16", 18, 64, 8760, (32, 64, 512)), (2, "bf16", 1, 32, 8, (16, 16, 512)), (2, "f16", 51, 256, 672, (16, 16, 512)),
+    (1, "bf16", 75, 64, 11656, (16, 128, 256)), (1, "bf16", 39, 64, 8408, (16, 128, 512)), (1, "f16", 20, 64, 10616, (32, 16, 256)), (1, "f16", 18, 64, 2352, (32, 16, 512)),
+    (1, "bf16", 69, 64, 10680, (16, 128, 256)), (1, "bf16", 305, 64, 1592, (32, 64, 512)), (2, "bf16", 1, 32, 8, (16, 16, 512)), (2, "f16", 51, 256, 672, (16, 16, 512)),
     (2, "bf16", 1, 40, 4128, (16, 64, 512)), (2, "f16", 19, 32, 9528, (16, 128, 512)), (2, "bf16", 2296, 32, 136, (32, 64, 512)), (2, "f16", 2179, 40, 168, (32, 64, 512))])
 def test_shallow_16_bit_calls_as_dispatched(op, dtype, M, K, N, form):
     import paper_2604_15272_amd as P

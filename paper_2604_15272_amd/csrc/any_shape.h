@@ -52,8 +52,8 @@ template <typename E> struct Piece<E, 1> {
 //   f16: two parts carry such a product (22 bits) without loss and a fp32 value to 2^-23, where it is 2^-14 or more; the second is 2^11 times as
 //   large as it should be, so that it does not run out of exponents before the first does, and has accumulators of its own.  Below 2^-14 the
 //   error is 2^-36, no more than the rounding of a fp32 sum that has products of 2^-11 among them; rows of x * g that have none of that size
-//   (small_products) are worked out in fp32.  Weights of a softmax, at most 1 and relative to each other, are therefore taken kWeightScale times as large, their
-//   sums too: 2^-23 of a weight down to 2^-29 of the largest, 2^-51 of the largest below.
+//   (small_products) are worked out in fp32.  Weights of a softmax, at most 1 and relative to each other, are therefore taken kWeightScale
+//   times as large, their sums too: 2^-23 of a weight down to 2^-29 of the largest, 2^-51 of the largest below.
 // Infinities, NaNs and what rounds to an infinity have no parts: the sum is not finite then.
 template <typename S> struct PartProduct;
 template <> struct PartProduct<StoreBf16> {

@@ -21,9 +21,9 @@
 // Of that, neighbouring column tiles on one XCD (xcd_run_tile): bf16 8 x 4096 x 32003 60.7 -> 54.0 us, fp32 1 x 4096 x 4096
 // (stripes of 64 bytes, two to a cache line) 21.2 -> 13.5 us, fp32 16 x 4096 x 11000 38.3 -> 30.6 us.
 //
-// 16-bit storage in parts against the fp32 instructions, whose products took 27 us of it: bf16 8 x 4096 x 32003 54.9 -> 43.5 us, gated bf16 8 x 4096 x 14331
-// 60.0 -> 48.8, f16 8 x 4096 x 32003 54.2 -> 48.6, bf16 40 x 4193 x 8041 51.8 -> 39.0, 169 x 500 x 3001 15.7 -> 12.7.  (fp32 storage would
-// need six products of three parts each, with w split anew for every 16 rows: no gain.)
+// 16-bit storage in parts against the fp32 instructions, whose products took 27 us of it: bf16 8 x 4096 x 32003 54.9 -> 43.5 us, gated bf16 8 x
+// 4096 x 14331 60.0 -> 48.8, f16 8 x 4096 x 32003 54.2 -> 45.2, bf16 40 x 4193 x 8041 51.8 -> 36.8, 169 x 500 x 3001 15.7 -> 9.2.  (fp32
+// storage would need six products of three parts each, with w split anew for every 16 rows: no gain.)
 // Values that have no parts (infinities, NaNs, x * g past the format's range) make sums that are not finite; a wavefront that met one works its
 // outputs out once more with the fp32 instructions, at a bounded price (a NaN in the gain: bf16 8 x 4096 x 32003 40 -> 940 us).
 //
@@ -45,10 +45,10 @@ template <typename E, int XV, int VW, int RG, int G> struct Block {
     Piece<E, VW> w[G][XV];
 };
 
-// K from which 16 x 16 tiles of one 16-bit matrix request a block ahead.  There are few wavefronts then, and each walks ten blocks or more with nothing but the
-// others of its SIMD to hide the loads (us, ahead / one block at a time: f16 12 x 3501 x 41 13.1 / 15.0, 100 x 6001 x 500 23.0 / 25.7, bf16
-// 189 x 3501 x 83 14.8 / 16.0, 16 x 2601 x 1287 11.1 / 11.3; shorter and no better on average: f16 189 x 2049 x 83 11.4 / 10.1, 16 x 1801 x 1287 8.5 / 9.1,
-// bf16 100 x 601 x 500 5.2 / 5.0; two matrices: 0.82 of the time of two blocks with one, K 512 to 4096, 0.93 beyond).
+// K from which 16 x 16 tiles of one 16-bit matrix request a block ahead.  There are few wavefronts then, and each walks ten blocks or more with
+// nothing but the others of its SIMD to hide the loads (us, ahead / one block at a time: f16 12 x 3501 x 41 13.1 / 15.0, 100 x 6001 x 500 23.0 /
+// 25.7, bf16 189 x 3501 x 83 14.8 / 16.0, 16 x 2601 x 1287 11.1 / 11.3; shorter and no better on average: f16 189 x 2049 x 83 11.4 / 10.1, 16 x
+// 1801 x 1287 8.5 / 9.1, bf16 100 x 601 x 500 5.2 / 5.0; two matrices: 0.82 of the time of two blocks with one, K 512 to 4096, 0.93 beyond).
 constexpr int kNarrowAheadK = 2560;
 
 }  // namespace
@@ -193,9 +193,10 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
     // one is asked for again.  A condition or a copy between a load and its use makes the compiler wait for the load there
     // (fp32 64 x 4096 x 4096 30.2 -> 27.0 us without; three blocks: the same, bf16 8 x 4096 x 32003 8 % slower).
     // In parts, one block at a time: in half the registers (and half the code, of which a short call runs little) more wavefronts share a SIMD: gated
-    // bf16 13 x 256 x 1920 4.5 -> 3.9 us, bf16 8 x 512 x 1024 4.6 -> 3.9, 8 x 4096 x 32003 45.3 -> 43.5, gated 8 x 4096 x 14331 51.6 -> 48.8; 27 x 704
-    // x 2880 7.0 -> 7.2.  f16 and wide tiles: all loads of a block before its products, which the compiler else mixes (f16 8 x 4096 x 32003 50.9 us mixed, 45.2
-    // so; gated 8 x 4096 x 14331 56.0 / 50.6; narrow tiles lose 2 %).  (fp32 39 x 5568 x 960 would take 76 us instead of 22.)
+    // bf16 13 x 256 x 1920 4.5 -> 3.9 us, bf16 8 x 512 x 1024 4.6 -> 3.9, 8 x 4096 x 32003 45.3 -> 43.5, gated 8 x 4096 x 14331 51.6 -> 48.8; 27
+    // x 704 x 2880 7.0 -> 7.2.  f16 and wide tiles: all loads of a block before its products, which the compiler else mixes (f16 8 x 4096 x
+    // 32003 50.9 us mixed, 45.2 so; gated 8 x 4096 x 14331 56.0 / 50.6; narrow tiles lose 2 %).  (fp32 39 x 5568 x 960 would take 76 us instead
+    // of 22.)
     const int nfull = K / KB;
     if constexpr (!AHEAD) {
         for (int kb = wave; kb < nfull; kb += nw) {

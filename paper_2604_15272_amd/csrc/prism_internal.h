@@ -10,7 +10,7 @@
 
 namespace prism {
 
-// The fp32 matrix-core kernels for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
+// The matrix-core kernels of 32-bit precision for any shape and storage type: 16-row groups and columns per lane (a workgroup has 16
 // times as many), wavefronts that share K.  From kTiledRowGroups row groups on: the kernel with both operands in LDS.
 constexpr int kTiledRowGroups = 4;
 constexpr int general_max_waves(int row_groups, int cols) { return row_groups * cols == 1 ? 16 : 8; }
@@ -29,7 +29,7 @@ struct Call {
     bool gated;
     int flags;  // kFlag* bits
     hipStream_t stream;
-    GeneralForm form;  // of the fp32 kernel, where the call takes that path
+    GeneralForm form;  // of the kernel for any shape, where the call takes that path
     bool tile_runs;    // multi-row decode kernel: column tiles in runs of neighbours, one run per XCD
 };
 
@@ -66,7 +66,7 @@ constexpr int kAttnMaxHeads = 16;
 constexpr int kAttnSliceKeys = 128;     // keys per workgroup for short contexts (one 32-key block per wavefront)
 constexpr int kAttnMaxSlices = 64;
 
-// The fp32 matrix-core attention kernel: query heads per workgroup, wavefronts.
+// The matrix-core attention kernel of 32-bit precision: query heads per workgroup, wavefronts.
 constexpr int kGqaGeneralHeads = 16;
 constexpr int kGqaGeneralWaves = 8;
 constexpr int kAttnThreads = 256;       // of the other two attention kernels
@@ -76,7 +76,7 @@ struct AttentionPlan {
     int splits;      // key slices per batch entry
     int slice_keys;  // keys per slice (a multiple of 32)
     uint64_t workspace_bytes;
-    bool general;    // PRISM_PATH_SIMPLE: the fp32 matrix-core kernel, else the plain one
+    bool general;    // PRISM_PATH_SIMPLE: the matrix-core kernel of 32-bit precision, else the plain one
 };
 
 struct AttentionWorkspace {

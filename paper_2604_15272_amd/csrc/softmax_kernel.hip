@@ -16,7 +16,7 @@
 // actually bound by at the paper's shape is the vector pipe (exponentials, conversions, the permutes
 // of W, which every workgroup re-reads from the L2 for its 16 rows).
 //
-// Any shape and storage type: the same in fp32 (softmax_general_kernel).
+// Any shape and storage type: the same with 32-bit weights and sums (softmax_general_kernel).
 #include <type_traits>
 
 #include "any_shape.h"
@@ -225,14 +225,15 @@ hipError_t launch_softmax_rows_16bit(const SoftmaxCall& c, bool f16) {
 // wavefronts take 32-deep K-blocks round-robin, lane (q, c) holds eight consecutive K values of row c and the same eight rows
 // of W at its VW columns.  Products: fp32 storage on the matrix cores in fp32, 16-bit storage on the 16-bit ones, the weight as parts (three of
 // bf16 carry it whole, two of f16 to 2^-23 from 2^-29 of the largest weight on and to 2^-51 of the largest below; PartProduct in any_shape.h).
-// The softmax rides in the operand: a running maximum per row and wavefront (its accumulators are rescaled when it moves), the exponentials in registers, their row sums in fp32
-// beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
+// The softmax rides in the operand: a running maximum per row and wavefront (its accumulators are rescaled when it moves), the exponentials in
+// registers, their row sums in fp32 beside the products; the wavefronts' partials meet in LDS relative to the common maximum.
 // The kernel this replaces (8 rows x 256 columns, one thread per column, two passes over X) was bound by its serial loads:
-// fp32 1624 x 3008 x 352 794 us, now 75 to 81 us.
+// fp32 1624 x 3008 x 352 794 us, now 65 us.
 // Bound now: nothing single.  fp32 4096 x 4096 x 128 takes 62 to 69 us, 62 to 69 of 157 TFLOP/s: the matrix cores are busy 46 % of the cycles
 // in which a compute unit has a workgroup, beside 17e6 exponentials for every column tile and operands straight from the
 // caches.  With few workgroups it is the chain of a wavefront's blocks.  16-bit storage, in parts against the fp32 instructions: f16
-// 372 x 14151 x 393 112 -> 82 us, bf16 2048 x 2049 x 513 96 -> 65, 4000 x 513 x 129 27.3 -> 20.5 (the exponentials and the weights' parts bound it).
+// 372 x 14151 x 393 112 -> 81 us, and with one block at a time bf16 2048 x 2049 x 513 96 -> 51, 4000 x 513 x 129 27.3 -> 13.1 (the
+// exponentials and the weights' parts bound it).
 template <typename S, int RG, int VW, bool AHEAD>
 __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_general_kernel(const typename S::elem* __restrict__ X,
                                                                             const typename S::elem* __restrict__ W,
@@ -369,8 +370,8 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void softmax_genera
         }
     };
     // AHEAD: two named blocks in turn, without a condition between a load and its use (general_kernel.hip), for one round of workgroups with a
-    // deep K, which has nothing else to wait under (bf16 8 x 16383 x 67 53.2 us, 57.5 without; fp32 4096 x 4096 x 128 62.7 / 63.7).  Elsewhere one block at
-    // a time: in half the registers more wavefronts share a SIMD (bf16 4000 x 513 x 129 20.6 -> 13.3, 2048 x 2049 x 513 65 -> 52, fp32
+    // deep K, which has nothing else to wait under (bf16 8 x 16383 x 67 53.2 us, 57.5 without; fp32 4096 x 4096 x 128 62.7 / 63.7).  Elsewhere
+    // one block at a time: in half the registers more wavefronts share a SIMD (bf16 4000 x 513 x 129 20.6 -> 13.3, 2048 x 2049 x 513 65 -> 52, fp32
     // 1624 x 3008 x 352 74.6 -> 65.1, 45 x 512 x 192 5.9 -> 5.3).
     const int nfull = K / KBG;
     if constexpr (!AHEAD) {

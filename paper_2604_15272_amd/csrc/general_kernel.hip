@@ -272,20 +272,18 @@ __global__ __launch_bounds__(general_max_waves(RG, VW) * 64) void general_kernel
             const int m = m0 + 16 * r + row, n = column(col);
             if (m >= M || n < 0) continue;
             float v = 0.f, u = 0.f, tot = 0.f;
+            float seen = 0.f;  // f16: above 0 if some wavefront saw a product that is not too small
             for (int w = 0; w < nw; ++w) {
                 v += red[(w * 16 + row) * TN + col];
                 if (GATED) u += red[((nw + w) * 16 + row) * TN + col];
                 const float squares = ss_red[w * (16 * RG) + 16 * r + row];
                 tot += F16_PARTS ? fabsf(squares) : squares;
+                if (F16_PARTS) seen = fmaxf(seen, squares);
             }
             const float rinv = (flags & kFlagNorm) ? 1.0f / sqrtf(tot / (float)K + eps) : 1.0f;
             // (A row whose 1/rms is a NaN is one anyway.)
             if (PARTS && !__builtin_isfinite(GATED ? fabsf(v) + fabsf(u) : v) && rinv == rinv) bad = true;
-            if (F16_PARTS && gain) {
-                float seen = 0.f;  // above 0 if some wavefront saw a product that is not too small
-                for (int w = 0; w < nw; ++w) seen = fmaxf(seen, ss_red[w * (16 * RG) + 16 * r + row]);
-                bad = bad | ((seen == 0.f) & (tot > 0.f));
-            }
+            if (F16_PARTS) bad = bad | ((seen == 0.f) & (tot > 0.f));  // (without a gain no sign is set)
             float y = v * rinv;
             if (GATED) {
                 const float a = y;

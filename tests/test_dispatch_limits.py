@@ -1,0 +1,18 @@
+"""Limits between kernels and forms, on 256 compute units, with the times that put them there."""
+import pytest
+
+
+@pytest.fixture()
+def P():
+    import paper_2604_15272_amd as P
+    P.prism_diag_set_cu_count(256)
+    yield P
+    P.prism_diag_set_cu_count(0)
+
+
+def test_f16_softmax_of_very_shallow_k_and_many_outputs_on_the_rows_kernel(P):
+    path = lambda dtype, M, K, N: P.prism_plan(P.PRISM_OP_SOFTMAX_MATMUL, M, K, N, dtype)["path"]
+    for M, N in ((3745, 2072), (2633, 7368), (6067, 2936), (4676, 5504)):   # us: 41.5 / 62.0 on the kernel for any shape, 96 / 145, 91 / 134, 125 / 191
+        assert path(P.PRISM_F16, M, 32, N) == P.PRISM_PATH_ROWS
+    assert path(P.PRISM_F16, 480, 32, 4496) == P.PRISM_PATH_SIMPLE    # 23.0 / 19.6
+    assert path(P.PRISM_BF16, 7263, 32, 4240) == P.PRISM_PATH_SIMPLE  # 168 / 139

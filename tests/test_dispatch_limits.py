@@ -16,3 +16,9 @@ def test_f16_softmax_of_very_shallow_k_and_many_outputs_on_the_rows_kernel(P):
         assert path(P.PRISM_F16, M, 32, N) == P.PRISM_PATH_ROWS
     assert path(P.PRISM_F16, 480, 32, 4496) == P.PRISM_PATH_SIMPLE    # 23.0 / 19.6
     assert path(P.PRISM_BF16, 7263, 32, 4240) == P.PRISM_PATH_SIMPLE  # 168 / 139
+
+
+def test_few_workgroups_of_two_narrow_matrices(P):
+    for M, K, N in ((1, 1536, 8), (8, 1536, 24), (8, 1792, 24)):   # us from HBM: 5.1 / 7.3 on the decode kernel, 6.9 / 7.9, 7.8 / 8.2
+        assert P.prism_plan(1, M, K, N, P.PRISM_BF16)["path"] == P.PRISM_PATH_SIMPLE
+    assert P.prism_plan(1, 8, 1792, 1024, P.PRISM_BF16)["path"] == P.PRISM_PATH_DECODE   # 13.6 / 10.1
